@@ -7,6 +7,7 @@
 
 #include "adjoint_grad.h"
 #include "internal.h"
+#include "strided_sum.h"
 
 namespace bb {
 
@@ -19,9 +20,7 @@ static __device__ __align__(256) double scratch[kGradScratchBytes / sizeof(doubl
 
 namespace {
 
-constexpr int kGradR = 4;          // systems per lane in the band-gradient kernel
-constexpr int kGradRows = 32;      // rows per wave strip
-constexpr int kGradSys = kWave * kGradR;
+constexpr int kGradRows = 8;       // rows per wave strip of the band-gradient kernel
 
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -30,13 +29,18 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// One wave: rows [i0, i0 + kGradRows) x the k-blocks kg*kpw .. (kg+1)*kpw - 1
-// of kGradSys systems each (blockIdx.x = kg).
-// part[kg][band][i] = -sum over those systems of lam[i,k] x[i+off,k], the
-// k-blocks added in ascending order.  Within a k-block the loads of row i+1
-// are issued before row i is reduced (one row in flight ahead); lane i - i0
-// keeps row i's sum and the strip is stored at the end, one coalesced store
-// per band.
+// One wave: rows [i0, i0 + 8) x the 64-system blocks kg*kpw .. (kg+1)*kpw - 1
+// (blockIdx.x = kg): part[kg][band][i] = -sum over those systems of
+// lam[i,k] x[i+off,k].
+//
+// Bound by HBM (lam and x read once each).  Every lane keeps the 8 (2K+1)
+// products of its systems in registers over all of the wave's blocks, with a
+// whole block (8 rows of lam, 8 + 2K of x) in flight at once, and the lanes
+// are added once, at the end: three halving rounds leave the eight lanes of
+// octet r row r's sums (24 or 40 values in 21 or 35 shuffles), a butterfly
+// inside the octet finishes.  Reducing every row of every block by a full
+// butterfly per band in 32-row strips took 41.8 us at n = 512, m = 8192,
+// pentadiagonal (67 MB: 1.6 TB/s; 512 waves).
 template <int NB>
 __global__ __launch_bounds__(256) void band_grad_partial(int n, int cyclic, int64_t m, int64_t ld,
                                                          int64_t kpw,
@@ -44,112 +48,90 @@ __global__ __launch_bounds__(256) void band_grad_partial(int n, int cyclic, int6
                                                          const double *__restrict__ x,
                                                          double *__restrict__ part)
 {
-    static_assert(kGradRows <= kWave, "one row per lane at the store");
-    constexpr int H = NB / 2;
+    constexpr int H = NB / 2, R = kGradRows;
+    static_assert(R == 8, "three halving rounds over lane bits 5, 4, 3");
     const int lane = threadIdx.x % kWave;
     const int strip = blockIdx.y * (blockDim.x / kWave) + threadIdx.x / kWave;
-    const int i0 = strip * kGradRows;
-    if (i0 >= n) return;
-    const int i1 = i0 + kGradRows < n ? i0 + kGradRows : n;
-    const int64_t kblocks = (m + kGradSys - 1) / kGradSys;
+    const int i0 = strip * R;
+    if (i0 >= n) return;   // whole waves
+    const int64_t kblocks = (m + kWave - 1) / kWave;
     const int64_t kb0 = (int64_t)blockIdx.x * kpw;
     const int64_t kb1 = kb0 + kpw < kblocks ? kb0 + kpw : kblocks;
-    double keep[NB];
+    double v[R * NB];
 #pragma unroll
-    for (int q = 0; q < NB; ++q) keep[q] = 0.0;
+    for (int e = 0; e < R * NB; ++e) v[e] = 0.0;
+    // rows past either end: row n-1 or 0 in bounds (their products are
+    // dropped at the store), or mod n when periodic (n >= 2K+1)
+    auto row_of = [&](int i) -> int64_t {
+        if (cyclic) return i < 0 ? i + n : (i >= n ? (i - n) % n : i);
+        return i < 0 ? 0 : (i >= n ? n - 1 : i);
+    };
     for (int64_t kb = kb0; kb < kb1; ++kb) {
-        int64_t ks[kGradR];
-        bool kv[kGradR];
+        const int64_t k = kb * kWave + lane;
+        const bool kval = k < m;
+        const int64_t kk = kval ? k : m - 1;
+        double l[R], w[R + 2 * H];
 #pragma unroll
-        for (int r = 0; r < kGradR; ++r) {
-            ks[r] = kb * kGradSys + r * kWave + lane;
-            kv[r] = ks[r] < m;
-        }
-        auto load_x = [&](int row, int r) -> double {
-            if (row < 0 || row >= n) {
-                if (!cyclic) return 0.0;
-                row = (row % n + n) % n;
-            }
-            return kv[r] ? x[(int64_t)row * ld + ks[r]] : 0.0;
-        };
-        auto load_l = [&](int row, int r) -> double {
-            return (kv[r] && row < n) ? lam[(int64_t)row * ld + ks[r]] : 0.0;
-        };
-        // sliding window of x rows i-H .. i+H, and the next row's operands
-        double win[NB][kGradR], xn[kGradR], ln[kGradR];
+        for (int t = 0; t < R + 2 * H; ++t) w[t] = x[row_of(i0 + t - H) * ld + kk];
 #pragma unroll
-        for (int w = 0; w < NB - 1; ++w)
+        for (int t = 0; t < R; ++t) l[t] = lam[(int64_t)(i0 + t < n ? i0 + t : n - 1) * ld + kk];
 #pragma unroll
-            for (int r = 0; r < kGradR; ++r) win[w + 1][r] = load_x(i0 - H + w, r);
+        for (int t = 0; t < R + 2 * H; ++t) w[t] = kval ? w[t] : 0.0;
 #pragma unroll
-        for (int r = 0; r < kGradR; ++r) {
-            xn[r] = load_x(i0 + H, r);
-            ln[r] = load_l(i0, r);
-        }
-        for (int i = i0; i < i1; ++i) {
-            double l[kGradR];
+        for (int t = 0; t < R; ++t) {
+            const double lt = kval ? l[t] : 0.0;
 #pragma unroll
-            for (int r = 0; r < kGradR; ++r) {
-#pragma unroll
-                for (int w = 0; w < NB - 1; ++w) win[w][r] = win[w + 1][r];
-                win[NB - 1][r] = xn[r];
-                l[r] = ln[r];
-            }
-            if (i + 1 < i1) {
-#pragma unroll
-                for (int r = 0; r < kGradR; ++r) {
-                    xn[r] = load_x(i + 1 + H, r);
-                    ln[r] = load_l(i + 1, r);
-                }
-            }
-            double acc[NB];
-#pragma unroll
-            for (int q = 0; q < NB; ++q) acc[q] = 0.0;
-#pragma unroll
-            for (int r = 0; r < kGradR; ++r)
-#pragma unroll
-                for (int q = 0; q < NB; ++q) acc[q] = fma(l[r], win[q][r], acc[q]);
-#pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                const double sum = wave_sum(acc[q]);
-                if (lane == i - i0) keep[q] -= sum;
-            }
+            for (int q = 0; q < NB; ++q) v[t * NB + q] = fma(lt, w[t + q], v[t * NB + q]);
         }
     }
-    double *dst = part + (int64_t)blockIdx.x * NB * n;
-    if (lane < i1 - i0) {
-        const int i = i0 + lane;
+    // halving: a lane with the bit clear keeps the lower half of the rows
+    double h4[4 * NB], h2[2 * NB], h1[NB];
+    const bool b5 = (lane & 32) != 0, b4 = (lane & 16) != 0, b3 = (lane & 8) != 0;
+#pragma unroll
+    for (int e = 0; e < 4 * NB; ++e)
+        h4[e] = (b5 ? v[e + 4 * NB] : v[e]) + __shfl_xor(b5 ? v[e] : v[e + 4 * NB], 32, kWave);
+#pragma unroll
+    for (int e = 0; e < 2 * NB; ++e)
+        h2[e] = (b4 ? h4[e + 2 * NB] : h4[e]) + __shfl_xor(b4 ? h4[e] : h4[e + 2 * NB], 16, kWave);
+#pragma unroll
+    for (int e = 0; e < NB; ++e) {
+        h1[e] = (b3 ? h2[e + NB] : h2[e]) + __shfl_xor(b3 ? h2[e] : h2[e + NB], 8, kWave);
+        for (int off = 4; off > 0; off >>= 1) h1[e] += __shfl_xor(h1[e], off, kWave);
+    }
+    const int i = i0 + (lane >> 3);
+    if ((lane & 7) == 0 && i < n) {
+        double *dst = part + (int64_t)blockIdx.x * NB * n;
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             // entries outside a non-cyclic matrix have no gradient
             const bool inside = cyclic || (i + q - H >= 0 && i + q - H < n);
-            dst[(int64_t)q * n + i] = inside ? keep[q] : 0.0;
+            dst[(int64_t)q * n + i] = inside ? -h1[q] : 0.0;
         }
     }
 }
 
-// grad[e] += sum over the partial groups g of part[g][e]: the 16 waves of a
-// block each sum every 16th group (ascending), and the 16 sums are added in
-// a fixed order -- the same result on every run.
-constexpr int kFoldSubs = 16;
-__global__ __launch_bounds__(kFoldSubs * kWave) void band_grad_fold(int64_t total, int64_t groups,
-                                                                  const double *__restrict__ part,
-                                                                  double *__restrict__ grad)
+// grad[e] += sum over the partial groups g of part[g][e].  A block sums 16
+// entries with 64 rows of threads: row r takes every 64th group (four at a
+// time, in order), the 64 sums are added in a fixed order -- the same result
+// on every run.  The partial sums of a rollout's segment (2048 groups x 3072
+// entries, 50 MB) fold in this many blocks with 32 loads a thread; 64 entries
+// and 16 rows a block took 61 us (48 blocks, 128 loads a thread).
+constexpr int kFoldEntries = 16, kFoldSubs = 64;
+__global__ __launch_bounds__(kFoldEntries * kFoldSubs) void band_grad_fold(
+    int64_t total, int64_t groups, const double *__restrict__ part, double *__restrict__ grad)
 {
-    __shared__ double red[kFoldSubs][kWave];
-    const int lane = threadIdx.x % kWave, sub = threadIdx.x / kWave;
-    const int64_t e = (int64_t)blockIdx.x * kWave + lane;
+    __shared__ double red[kFoldSubs][kFoldEntries + 1];
+    const int lane = threadIdx.x % kFoldEntries, sub = threadIdx.x / kFoldEntries;
+    const int64_t e = (int64_t)blockIdx.x * kFoldEntries + lane;
     double s = 0.0;
-    if (e < total)
-        for (int64_t g = sub; g < groups; g += kFoldSubs) s += part[g * total + e];
+    if (e < total) s = strided_sum(part + e, total, sub, groups, kFoldSubs);
     red[sub][lane] = s;
     __syncthreads();
-    if (sub == 0 && e < total) {
-        double t = red[0][lane];
-#pragma unroll
-        for (int q = 1; q < kFoldSubs; ++q) t += red[q][lane];
-        grad[e] += t;
+    for (int w = kFoldSubs / 2; w > 0; w >>= 1) {
+        if (sub < w) red[sub][lane] += red[sub + w][lane];
+        __syncthreads();
     }
+    if (sub == 0 && e < total) grad[e] += red[0][lane];
 }
 
 // ---------------------------------------------------------------- MSE
@@ -187,16 +169,18 @@ __global__ __launch_bounds__(256) void mse_partial(int64_t n, int64_t m, int64_t
     }
 }
 
-__global__ __launch_bounds__(256) void mse_fold(int64_t parts, double scale,
-                                                const double *__restrict__ part,
-                                                double *__restrict__ loss)
+// The partial sums (one per row and 1024 systems: 65536 at n = 1024,
+// m = 2^16) added by one block in a fixed order, four loads in flight a
+// thread; 256 threads with one took 94 us there.
+constexpr int kMseFoldThreads = 1024;
+__global__ __launch_bounds__(kMseFoldThreads) void mse_fold(int64_t parts, double scale,
+                                                            const double *__restrict__ part,
+                                                            double *__restrict__ loss)
 {
-    __shared__ double red[256];
-    double s = 0.0;
-    for (int64_t e = threadIdx.x; e < parts; e += 256) s += part[e];
-    red[threadIdx.x] = s;
+    __shared__ double red[kMseFoldThreads];
+    red[threadIdx.x] = strided_sum(part, 1, threadIdx.x, parts, kMseFoldThreads);
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
+    for (int w = kMseFoldThreads / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
@@ -301,19 +285,20 @@ hipError_t launch_copy_tiles(const void *src, void *dst, int64_t bytes, hipStrea
     return hipGetLastError();
 }
 
-// k-blocks per wave: enough waves (about 8192, four per SIMD on 256 CUs) to
-// keep HBM busy, few enough partial sums that the fold stays short.
+// 64-system blocks per wave: enough waves (about 8192, eight per SIMD) to
+// keep HBM busy, few enough partial sums that the fold stays short (at most
+// 64 groups of them for n >= 1024).
 int64_t band_grad_kpw(int n, int64_t m)
 {
-    const int64_t kblocks = (m + kGradSys - 1) / kGradSys;
+    const int64_t kblocks = (m + kWave - 1) / kWave;
     const int64_t strips = (n + kGradRows - 1) / kGradRows;
-    int64_t kpw = kblocks * strips / 8192;
+    const int64_t kpw = (kblocks * strips + 8191) / 8192;
     return kpw < 1 ? 1 : kpw;
 }
 
 size_t band_grad_workspace(int nb, int n, int64_t m)
 {
-    const int64_t kblocks = (m + kGradSys - 1) / kGradSys;
+    const int64_t kblocks = (m + kWave - 1) / kWave;
     const int64_t kpw = band_grad_kpw(n, m);
     const int64_t groups = (kblocks + kpw - 1) / kpw;
     return (size_t)groups * nb * n * sizeof(double);
@@ -325,7 +310,7 @@ hipError_t band_grad_launch(int nb, bool cyclic, int n, int64_t m, int64_t ld, c
                             const double *x, double *grad, double *part, int64_t kpw,
                             hipStream_t s)
 {
-    const int64_t kblocks = (m + kGradSys - 1) / kGradSys;
+    const int64_t kblocks = (m + kWave - 1) / kWave;
     const int64_t groups = (kblocks + kpw - 1) / kpw;
     const int strips = (n + kGradRows - 1) / kGradRows;
     const int waves = 256 / kWave;
@@ -339,8 +324,8 @@ hipError_t band_grad_launch(int nb, bool cyclic, int n, int64_t m, int64_t ld, c
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t total = (int64_t)nb * n;
-    hipLaunchKernelGGL(band_grad_fold, dim3((unsigned)((total + kWave - 1) / kWave)),
-                       dim3(kFoldSubs * kWave), 0, s, total, groups, (const double *)part, grad);
+    hipLaunchKernelGGL(band_grad_fold, dim3((unsigned)((total + kFoldEntries - 1) / kFoldEntries)),
+                       dim3(kFoldEntries * kFoldSubs), 0, s, total, groups, (const double *)part, grad);
     return hipGetLastError();
 }
 
@@ -383,7 +368,7 @@ hipError_t launch_band_grad_scratch(int nb, bool cyclic, int n, int64_t m, int64
 {
     const int64_t cap = (int64_t)(kGradScratchBytes / sizeof(double)) / ((int64_t)nb * n);
     if (cap < 1) return hipErrorInvalidValue;   // the host checks nb * n first
-    const int64_t kblocks = (m + kGradSys - 1) / kGradSys;
+    const int64_t kblocks = (m + kWave - 1) / kWave;
     int64_t kpw = band_grad_kpw(n, m);
     if ((kblocks + kpw - 1) / kpw > cap) kpw = (kblocks + cap - 1) / cap;
     double *part = nullptr;
@@ -396,8 +381,8 @@ hipError_t launch_grad_fold(int64_t total, int64_t groups, const double *part, d
                             hipStream_t s)
 {
     if (total <= 0 || groups <= 0) return hipSuccess;
-    hipLaunchKernelGGL(band_grad_fold, dim3((unsigned)((total + kWave - 1) / kWave)),
-                       dim3(kFoldSubs * kWave), 0, s, total, groups, part, grad);
+    hipLaunchKernelGGL(band_grad_fold, dim3((unsigned)((total + kFoldEntries - 1) / kFoldEntries)),
+                       dim3(kFoldEntries * kFoldSubs), 0, s, total, groups, part, grad);
     return hipGetLastError();
 }
 
@@ -416,7 +401,7 @@ hipError_t launch_mse(const double *u, const double *target, double *grad, doubl
                        dim3(256), 0, s, (int64_t)n, m, ld, scale, u, target, grad, (double *)ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mse_fold, dim3(1), dim3(256), 0, s, (int64_t)n * cols, scale,
+    hipLaunchKernelGGL(mse_fold, dim3(1), dim3(kMseFoldThreads), 0, s, (int64_t)n * cols, scale,
                        (const double *)ws, loss);
     return hipGetLastError();
 }
