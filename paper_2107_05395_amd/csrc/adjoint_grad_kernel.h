@@ -135,7 +135,7 @@ void adjoint_grad_kernel(const double *__restrict__ table, int64_t table_elems, 
     extern __shared__ double smem_d[];
     const int64_t tl = SCALAR ? 0 : table_elems;
     double *xch = smem_d + tl;
-    double *stage = xch + split_exchange_len(QL) + (int64_t)(threadIdx.x / kWave) * grad_stage_len<K, SL>();
+    double *stage = xch + split_exchange_len(K, QL) + (int64_t)(threadIdx.x / kWave) * grad_stage_len<K, SL>();
     typename Src::ptr tab;
     if constexpr (SCALAR) {
         tab = (typename Src::ptr)table;
@@ -145,8 +145,8 @@ void adjoint_grad_kernel(const double *__restrict__ table, int64_t table_elems, 
         tab = smem_d;
     }
 
-    LaneGeom lg = lane_geom(SCALAR ? QL : g.log2P, QL);
-    if constexpr (SCALAR) lg.j = __builtin_amdgcn_readfirstlane(lg.j);
+    LaneGeom lg = lane_geom(SCALAR ? QL : QL + 6 - SL, QL);
+    if constexpr (SCALAR) lg.j = lg.j0;
     const int lane = threadIdx.x % kWave;
     const int n = g.n;
     const int row0 = lg.j * C;
@@ -203,7 +203,8 @@ void adjoint_grad_kernel(const double *__restrict__ table, int64_t table_elems, 
 #pragma unroll
             for (int t = 0; t < RB + 2 * K; ++t) win[t] = urow(t - K);
             __builtin_amdgcn_sched_barrier(0);
-            chunk_solve<double, K, C, CYC, true, Src>(c, tab, lg, n, 1, cq, xch);
+            chunk_solve<double, K, C, CYC, true, true, Src, !SCALAR, (SCALAR && QL < 2 ? 1 << QL : 4)>(
+                c, tab, lg, n, cq, xch);
             __builtin_amdgcn_sched_barrier(0);
             double nxt[RB];
 #pragma unroll

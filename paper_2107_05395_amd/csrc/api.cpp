@@ -192,9 +192,14 @@ struct StepPlan {
 // chunk per wave with scalar coefficients up to 8 chunks, else the LDS table
 // with 32 systems per group (4 waves at P = 8, 8 waves from P = 16; n = 1024,
 // m = 2^16: 0.063 vs 0.096 ms per tri step over one wave per group).
+// A tridiagonal group of 16 chunks that keeps its state on chip runs as 16
+// systems on 4 waves, three groups a CU (periodic n = 1024, m = 2^16, 50 steps:
+// 29 us a step against 34 with 32 systems on 8 waves, one group a CU, whose
+// waves all wait at its barriers together); with every state stored (states)
+// the rows' 256-byte segments of 32 systems matter more.
 // Tuning max_chunk, ch_uniform = 0 (no scalar kernel) and waves_per_system =
 // 1/2/4/8 override (tuning, testing).
-StepPlan step_plan(int64_t n, int64_t m)
+StepPlan step_plan(int K, int64_t n, int64_t m, bool states = false)
 {
     int C = bb::choose_chunk(n, std::min(max_chunk(BB_F64), bb::kChunkMaxCH));
     if (bb::tuning(bb::kTuneMaxChunk) < 0) {
@@ -221,7 +226,7 @@ StepPlan step_plan(int64_t n, int64_t m)
     if (pl.scalar)
         pl.log2Q = pl.log2P;
     else if (full && C >= 32 && pl.log2P >= 3)
-        pl.log2Q = pl.log2P >= 4 ? 3 : 2;
+        pl.log2Q = pl.log2P >= 4 && !(K == 1 && C == 64 && pl.log2P == 4 && !states) ? 3 : 2;
     if (bb::tuning(bb::kTuneWavesPerSystem) > 0 && !pl.scalar && full && C >= 32) {
         const int64_t q = bb::tuning(bb::kTuneWavesPerSystem);
         const int fl = q == 1 ? 0 : q == 2 ? 1 : q == 4 ? 2 : 3;
@@ -284,7 +289,8 @@ bb::LongGeom long_geom(const bb::Factor &f, int64_t m, int64_t ld, int C)
 // Decomposition, device table (the factor's own primal FP64 table for that
 // chunk size, shared with the solves) and launch geometry of a fused stepper.
 bb_status stepper_setup(bb::Factor &f, int dev, int64_t m, int64_t ld, StepPlan *pl,
-                        bb::DeviceTable *tab, bb::SweepGeom *g, bool adjoint = false);
+                        bb::DeviceTable *tab, bb::SweepGeom *g, bool adjoint = false,
+                        bool states = false);
 
 bb_status make(int kind, const double *a, const double *b, const double *c, const double *d,
                const double *e, int64_t n, bb_factor *out)
@@ -369,15 +375,15 @@ bb_status stepper_too_long(const bb::Factor &f)
 }
 
 bb_status stepper_setup(bb::Factor &f, int dev, int64_t m, int64_t ld, StepPlan *pl,
-                        bb::DeviceTable *tab, bb::SweepGeom *g, bool adjoint)
+                        bb::DeviceTable *tab, bb::SweepGeom *g, bool adjoint, bool states)
 {
     if (is_long(f)) return stepper_too_long(f);
-    *pl = step_plan(f.n, m);
+    *pl = step_plan(f.K, f.n, m, states);
     const int C = pl->C, P = pl->P;
     // the same table as a solve (or adjoint solve) with this chunk size
     const bb::Direction &dir = adjoint ? f.adjoint : f.primal;
     bb_status st = device_table(f, f.dev, std::make_tuple(dev, (int)adjoint, 0, C, 0), false,
-                                [&] { return bb::build_table(dir, f.K, f.cyclic, f.n, C, P); },
+                                [&] { return bb::build_sweep_table(dir, f.K, f.cyclic, f.n, C, P); },
                                 tab);
     if (st != BB_OK) return st;
     *g = step_geom(f.n, m, ld, *pl);
@@ -444,7 +450,7 @@ bb_status solve(bb_factor fh, const void *in, void *out, int64_t m, int64_t ld, 
     const bb::Direction &dir = adjoint ? f.adjoint : f.primal;
     bb::DeviceTable tab, band;
     st = device_table(f, f.dev, std::make_tuple(dev, (int)adjoint, (int)f32, C, 0), f32,
-                      [&] { return bb::build_table(dir, f.K, f.cyclic, f.n, C, P); }, &tab);
+                      [&] { return bb::build_sweep_table(dir, f.K, f.cyclic, f.n, C, P); }, &tab);
     if (st != BB_OK) return st;
     bb::Corners corners = f.corners;
     bb::Op op = bb::Op::Solve;
@@ -591,7 +597,7 @@ bb_status bb_factor_upload(bb_factor fh, void *stream)
             const bb::Direction &dir = adj ? f.adjoint : f.primal;
             bb::DeviceTable t;
             st = device_table(f, f.dev, std::make_tuple(dev, adj, f32, C, 0), f32 != 0,
-                              [&] { return bb::build_table(dir, f.K, f.cyclic, f.n, C, P); }, &t);
+                              [&] { return bb::build_sweep_table(dir, f.K, f.cyclic, f.n, C, P); }, &t);
             if (st != BB_OK) return st;
         }
     }
@@ -626,7 +632,7 @@ bb_status bb_plan(bb_factor fh, int64_t m, int32_t what, bb_precision p, int32_t
                         : p == BB_F32_RHS_REFINE ? bb::Op::RefineF32Rhs : bb::Op::Solve;
         log2Q = split_log2(log2P, C, (int)f.n, op, p == BB_F32_RHS_F64);
     } else {
-        const StepPlan pl = step_plan(f.n, m);
+        const StepPlan pl = step_plan(f.K, f.n, m);
         C = pl.C;
         P = pl.P;
         log2Q = pl.log2Q;
@@ -765,7 +771,7 @@ namespace {
 size_t ch_stats_bytes(int64_t n, int64_t m, int64_t samples)
 {
     if (samples < 1 || m < 1) return 0;
-    const StepPlan pl = step_plan(n, m);
+    const StepPlan pl = step_plan(2, n, m);
     const bb::SweepGeom g = step_geom(n, m, m, pl);
     return (size_t)g.groups * (size_t)samples * sizeof(double);
 }
@@ -973,7 +979,7 @@ bb_status cn_steps(bb_factor fh, const double *w, const double *c_in, double *ou
     StepPlan pl;
     bb::DeviceTable tab;
     bb::SweepGeom g;
-    if ((st = stepper_setup(f, dev, m, ld, &pl, &tab, &g, adjoint)) != BB_OK) return st;
+    if ((st = stepper_setup(f, dev, m, ld, &pl, &tab, &g, adjoint, traj || steps == 1)) != BB_OK) return st;
     double wk[5] = {0, 0, 0, 0, 0};
     for (int d = 0; d <= 2 * f.K; ++d) wk[d] = w[d];
     const bb::CyclicQ &q = adjoint ? f.adjoint.cor.q : f.primal.cor.q;
@@ -1033,10 +1039,10 @@ AdjGradPlan adjoint_grad_plan(const bb::Factor &f, int64_t m, int64_t ld)
     AdjGradPlan a;
     const int nb = 2 * f.K + 1;
     if (!is_long(f) && m > 0) {
-        a.pl = step_plan(f.n, m);
+        a.pl = step_plan(f.K, f.n, m, true);
         a.g = step_geom(f.n, m, ld, a.pl);
         if (bb::adjoint_grad_supported(f.K, a.g, a.pl.scalar)) {
-            const int64_t te = bb::table_len(f.K, f.cyclic, a.pl.C, a.pl.P);
+            const int64_t te = bb::sweep_table_len(f.K, f.cyclic, true, a.pl.C, a.pl.P);
             a.fused = bb::adjoint_grad_lds(f.K, a.g, a.pl.scalar, te) <= kLdsBytes;
         }
     }
@@ -1094,7 +1100,7 @@ bb_status bb_adjoint_band_grad(bb_factor fh, const double *g, const double *traj
         StepPlan pl;
         bb::DeviceTable tab;
         bb::SweepGeom geo;
-        if ((st = stepper_setup(f, dev, m, ld, &pl, &tab, &geo, true)) != BB_OK) return st;
+        if ((st = stepper_setup(f, dev, m, ld, &pl, &tab, &geo, true, true)) != BB_OK) return st;
         double *part = (double *)workspace;
         hipError_t e = bb::launch_adjoint_grad(f.K, f.cyclic, (const double *)tab.ptr, tab.elems,
                                                f.adjoint.cor.q, geo, pl.scalar, steps, g, traj,

@@ -11,6 +11,67 @@
 namespace bb {
 namespace {
 
+// Eight rows of a full chunk's stencil, in place, rows in order.  A row's
+// result takes its own register, so the rows after it have taken what they
+// need of it before (two, four rows at a time); left to the compiler the rows
+// of a chunk either sit in fenced blocks, each with a branch (64 tridiagonal
+// rows: 1536 clocks, 911 without), or hold a second copy of the chunk.  The
+// sums are the fma chains of StencilRhs.
+// K = 1: s enters as w0 c_{-1} + w1 c_0 of the first row and leaves as that of
+// the row after the eighth, r (old value).
+#define BB_W1_4(SA, SB, c0, c1, c2, c3, c4)                                                        \
+    "v_mul_f64 %[t1], %[w0], %[" c0 "]\n\tv_mul_f64 %[t2], %[w0], %[" c1 "]\n\t"                   \
+    "v_mul_f64 %[t3], %[w0], %[" c2 "]\n\tv_mul_f64 %[" SB "], %[w0], %[" c3 "]\n\t"               \
+    "v_fma_f64 %[t1], %[w1], %[" c1 "], %[t1]\n\tv_fma_f64 %[t2], %[w1], %[" c2 "], %[t2]\n\t"     \
+    "v_fma_f64 %[t3], %[w1], %[" c3 "], %[t3]\n\tv_fma_f64 %[" SB "], %[w1], %[" c4 "], %[" SB "]\n\t" \
+    "v_fma_f64 %[" c0 "], %[w2], %[" c1 "], %[" SA "]\n\t"                                         \
+    "v_fma_f64 %[" c1 "], %[w2], %[" c2 "], %[t1]\n\t"                                             \
+    "v_fma_f64 %[" c2 "], %[w2], %[" c3 "], %[t2]\n\t"                                             \
+    "v_fma_f64 %[" c3 "], %[w2], %[" c4 "], %[t3]\n\t"
+
+__device__ __forceinline__ void stencil_rows8(double *c, double r, double &s, const double (&w)[3])
+{
+    double sb, t1, t2, t3;
+    asm(BB_W1_4("sa", "sb", "c0", "c1", "c2", "c3", "c4") BB_W1_4("sb", "sa", "c4", "c5", "c6", "c7", "r")
+        : [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3]), [c4] "+v"(c[4]),
+          [c5] "+v"(c[5]), [c6] "+v"(c[6]), [c7] "+v"(c[7]), [sa] "+v"(s), [sb] "=&v"(sb),
+          [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3)
+        : [r] "v"(r), [w0] "s"(w[0]), [w1] "s"(w[1]), [w2] "s"(w[2]));
+}
+
+// K = 2: (u, v) enter as w0 c_{-2} + w1 c_{-1} and w0 c_{-1}, the first terms
+// of the first two rows, and leave as those of the two rows after the eighth;
+// r0, r1: those rows (old values).
+#define BB_W2_4(A, B, U, V, c0, c1, c2, c3, c4, c5)                                                \
+    "v_mul_f64 %[t2], %[w0], %[" c0 "]\n\tv_mul_f64 %[t3], %[w0], %[" c1 "]\n\t"                   \
+    "v_mul_f64 %[" U "], %[w0], %[" c2 "]\n\tv_fma_f64 %[" B "], %[w1], %[" c0 "], %[" B "]\n\t"   \
+    "v_mul_f64 %[" V "], %[w0], %[" c3 "]\n\tv_fma_f64 %[" A "], %[w2], %[" c0 "], %[" A "]\n\t"   \
+    "v_fma_f64 %[t2], %[w1], %[" c1 "], %[t2]\n\tv_fma_f64 %[t3], %[w1], %[" c2 "], %[t3]\n\t"     \
+    "v_fma_f64 %[" U "], %[w1], %[" c3 "], %[" U "]\n\tv_fma_f64 %[" B "], %[w2], %[" c1 "], %[" B "]\n\t" \
+    "v_fma_f64 %[" A "], %[w3], %[" c1 "], %[" A "]\n\t"                                           \
+    "v_fma_f64 %[t2], %[w2], %[" c2 "], %[t2]\n\tv_fma_f64 %[t3], %[w2], %[" c3 "], %[t3]\n\t"     \
+    "v_fma_f64 %[" B "], %[w3], %[" c2 "], %[" B "]\n\t"                                           \
+    "v_fma_f64 %[" c0 "], %[w4], %[" c2 "], %[" A "]\n\t"                                          \
+    "v_fma_f64 %[t2], %[w3], %[" c3 "], %[t2]\n\tv_fma_f64 %[t3], %[w3], %[" c4 "], %[t3]\n\t"     \
+    "v_fma_f64 %[" c1 "], %[w4], %[" c3 "], %[" B "]\n\t"                                          \
+    "v_fma_f64 %[" c2 "], %[w4], %[" c4 "], %[t2]\n\t"                                             \
+    "v_fma_f64 %[" c3 "], %[w4], %[" c5 "], %[t3]\n\t"
+
+__device__ __forceinline__ void stencil_rows8(double *c, double r0, double r1, double &u, double &v,
+                                              const double (&w)[5])
+{
+    double qa, qb, t2, t3;
+    asm(BB_W2_4("u", "v", "qa", "qb", "c0", "c1", "c2", "c3", "c4", "c5")
+        BB_W2_4("qa", "qb", "u", "v", "c4", "c5", "c6", "c7", "r0", "r1")
+        : [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3]), [c4] "+v"(c[4]),
+          [c5] "+v"(c[5]), [c6] "+v"(c[6]), [c7] "+v"(c[7]), [u] "+v"(u), [v] "+v"(v),
+          [qa] "=&v"(qa), [qb] "=&v"(qb), [t2] "=&v"(t2), [t3] "=&v"(t3)
+        : [r0] "v"(r0), [r1] "v"(r1), [w0] "s"(w[0]), [w1] "s"(w[1]), [w2] "s"(w[2]), [w3] "s"(w[3]),
+          [w4] "s"(w[4]));
+}
+#undef BB_W1_4
+#undef BB_W2_4
+
 // f_i = sum_{d=-K..K} w[d+K] c_{i+d}: the explicit half B of the scheme, a
 // constant stencil of 2K+1 weights.  Periodic (CYC): indices wrap mod n like
 // the matrix.  Otherwise the terms whose row falls outside the system are left
@@ -41,6 +102,21 @@ struct StencilRhs {
                 q1 = CYC ? h.e0 : 0.0;
                 q2 = CYC ? h.e1 : 0.0;
             }
+        }
+        if constexpr (FULL && C % 8 == 0) {
+            if constexpr (K == 1) {
+                double s = fma(w[1], c[0], w[0] * m1);
+#pragma unroll
+                for (int t = 0; t < C; t += 8)
+                    stencil_rows8(c + t, t + 8 < C ? c[t + 8 < C ? t + 8 : 0] : q1, s, w);
+            } else {
+                double u = fma(w[1], m1, w[0] * m2), v = w[0] * m1;
+#pragma unroll
+                for (int t = 0; t < C; t += 8)
+                    stencil_rows8(c + t, t + 8 < C ? c[t + 8 < C ? t + 8 : 0] : q1,
+                                  t + 8 < C ? c[t + 8 < C ? t + 9 : 0] : q2, u, v, w);
+            }
+            return;
         }
         // ragged: rows past n-1 of the system are rows 0, 1 (periodic) or absent
         const double past0 = CYC ? h.e0 : 0.0, past1 = CYC ? h.e1 : 0.0;

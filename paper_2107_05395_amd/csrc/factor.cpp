@@ -194,6 +194,10 @@ int make_factor_impl(int kind, const double *const bands[5], int64_t n, Factor &
         std::vector<double> U(n, 0.0), V(n, 0.0);
         U[0] = -b[0]; U[n - 1] = cw;
         V[0] = 1.0;  V[n - 1] = vlast;
+        f.primal.cor.u[0][0] = U[0];
+        f.primal.cor.u[3][0] = U[n - 1];
+        f.adjoint.cor.u[0][0] = V[0];
+        f.adjoint.cor.u[3][0] = V[n - 1];
         // primal: z = A'^{-1} U, s = (V.y) / (1 + V.z)
         std::vector<double> z = host_solve(f.primal.rec, 1, U);
         const double den = 1.0 + z[0] + vlast * z[n - 1];
@@ -243,6 +247,11 @@ int make_factor_impl(int kind, const double *const bands[5], int64_t n, Factor &
     u0[1] = -T[2]; u1[1] = -T[3];
     u0[n - 2] = Cb[0]; u1[n - 2] = Cb[1];
     u0[n - 1] = Cb[2]; u1[n - 1] = Cb[3];
+    const int64_t ends[4] = {0, 1, n - 2, n - 1};
+    for (int r = 0; r < 4; ++r) {
+        f.primal.cor.u[r][0] = u0[ends[r]];
+        f.primal.cor.u[r][1] = u1[ends[r]];
+    }
     std::vector<double> z0 = host_solve(f.primal.rec, 2, u0), z1 = host_solve(f.primal.rec, 2, u1);
     auto vt = [&](const std::vector<double> &y, int r) {   // (V^T y)_r
         return y[r] - (W[r * 2 + 0] * y[n - 2] + W[r * 2 + 1] * y[n - 1]);
@@ -267,6 +276,10 @@ int make_factor_impl(int kind, const double *const bands[5], int64_t n, Factor &
     v0[0] = 1.0; v1[1] = 1.0;
     v0[n - 2] = -W[0]; v0[n - 1] = -W[1];
     v1[n - 2] = -W[2]; v1[n - 1] = -W[3];
+    for (int r = 0; r < 4; ++r) {
+        f.adjoint.cor.u[r][0] = v0[ends[r]];
+        f.adjoint.cor.u[r][1] = v1[ends[r]];
+    }
     std::vector<double> w0 = host_solve(f.adjoint.rec, 2, v0), w1 = host_solve(f.adjoint.rec, 2, v1);
     // (U^T y)_r = -(T[0][r] y0 + T[1][r] y1) + Cb[0][r] y_{n-2} + Cb[1][r] y_{n-1}
     auto ut = [&](const std::vector<double> &y, int r) {
@@ -388,6 +401,167 @@ std::vector<double> build_table(const Direction &d, int K, bool cyclic, int64_t 
                 at(qz, j, t) = -d.cor.z0[row];
                 if (K == 2) at(qz + 1, j, t) = -d.cor.z1[row];
             }
+        }
+    }
+    return tab;
+}
+
+std::vector<double> build_sweep_table(const Direction &d, int K, bool cyclic, int64_t n, int C, int P)
+{
+    const int64_t L = (int64_t)P * (C + 1);
+    const bool full = (int64_t)P * C == n;
+    const int na = sweep_arrays(K, cyclic, full);
+    std::vector<double> tab((size_t)sweep_table_len(K, cyclic, full, C, P), 0.0);
+    const Recurrence &r = d.rec;
+    const int KK = K * K;
+    const int qE = 0, qS = K, qs = 2 * K, ql = 2 * K + 1, qu = 3 * K + 1, qz = 4 * K + 1;
+    double *Mf = tab.data() + na * L, *Mb = Mf + (int64_t)P * KK, *G = Mb + (int64_t)P * KK;
+    double *HZ = G + (int64_t)P * KK, *FZ = HZ + (int64_t)P * KK;   // periodic, full
+    const int64_t jl = (n - 1) / C;   // last real chunk
+
+    // one chunk's recurrence coefficients, signs as in the paper; 0 past its rows
+    std::vector<double> s(C), l1(C), l2(C), u1(C), u2(C), g(C + 2), p(C), y(C);
+    for (int64_t j = 0; j <= jl; ++j) {
+        const int64_t r0 = j * C;
+        const int nr = (int)(n - r0 < C ? n - r0 : C);
+        double *at = tab.data() + j * (C + 1);
+        for (int t = 0; t < C; ++t) {
+            const bool real = t < nr;
+            s[t] = real ? r.s[r0 + t] : 0.0;
+            l1[t] = real ? r.l1[r0 + t] : 0.0;
+            u1[t] = real ? r.u1[r0 + t] : 0.0;
+            l2[t] = real && K == 2 ? r.l2[r0 + t] : 0.0;
+            u2[t] = real && K == 2 ? r.u2[r0 + t] : 0.0;
+        }
+        // response of the state (x_start .. ) to an input y_t of the backward
+        // recurrence, then of a linear functional q_t of y to the right-hand
+        // side: w_t = s_t (q_t - l1_{t+1} w'_{t+1} - l2_{t+2} w'_{t+2})
+        auto weights = [&](auto q, double *dst) {
+            g[C] = g[C + 1] = 0.0;
+            for (int t = C - 1; t >= 0; --t) {
+                double v = q(t);
+                if (t + 1 < C) v -= l1[t + 1] * g[t + 1];
+                if (K == 2 && t + 2 < C) v -= l2[t + 2] * g[t + 2];
+                g[t] = v;
+                dst[t] = s[t] * v;
+            }
+        };
+        // end state: rows te, te-1 (the chunk's last rows; periodic and
+        // ragged: rows n-1, n-2 in the last real chunk)
+        const int te = cyclic && !full && j == jl ? nr - 1 : C - 1;
+        for (int c = 0; c < K; ++c)
+            if (te - c >= 0) weights([&](int t) { return t == te - c ? 1.0 : 0.0; }, at + (qE + c) * L);
+        auto backward_response = [&](int c) {   // p_t = d x_{start+c} / d y_t
+            for (int t = 0; t < C; ++t) {
+                double v = t == c ? 1.0 : 0.0;
+                if (t > c) {
+                    v -= u1[t - 1] * p[t - 1];
+                    if (K == 2 && t >= 2) v -= u2[t - 2] * p[t - 2];
+                }
+                p[t] = v;
+            }
+        };
+        for (int c = 0; c < K; ++c) {
+            backward_response(c);
+            weights([&](int t) { return p[t]; }, at + (qS + c) * L);
+        }
+        for (int c = 0; c < K; ++c) {
+            // history unit vector: end state (Mf) and backward start state (G)
+            double h1 = c == 0 ? 1.0 : 0.0, h2 = c == 1 ? 1.0 : 0.0;
+            for (int t = 0; t < C; ++t) {
+                double v = -l1[t] * h1;
+                if (K == 2) v -= l2[t] * h2;
+                y[t] = v;
+                h2 = h1;
+                h1 = v;
+            }
+            for (int e = 0; e < K; ++e)
+                Mf[j * KK + e * K + c] = te - e >= 0 ? y[te - e] : (c == e - te - 1 ? 1.0 : 0.0);
+            double g1 = 0.0, g2 = 0.0;
+            for (int t = C - 1; t >= 0; --t) {
+                double v = y[t] - u1[t] * g1;
+                if (K == 2) v -= u2[t] * g2;
+                g2 = g1;
+                g1 = v;
+            }
+            G[j * KK + c] = g1;
+            if (K == 2) G[j * KK + K + c] = g2;
+            // future unit vector: start state (Mb)
+            g1 = c == 0 ? 1.0 : 0.0;
+            g2 = c == 1 ? 1.0 : 0.0;
+            for (int t = C - 1; t >= 0; --t) {
+                double v = -u1[t] * g1;
+                if (K == 2) v -= u2[t] * g2;
+                g2 = g1;
+                g1 = v;
+            }
+            Mb[j * KK + c] = g1;
+            if (K == 2) Mb[j * KK + K + c] = g2;
+        }
+        // recurrence coefficients (off-diagonal ones and z negated: one fma per step)
+        for (int t = 0; t < nr; ++t) {
+            const int64_t row = r0 + t;
+            at[qs * L + t] = s[t];
+            at[ql * L + t] = -l1[t];
+            at[qu * L + t] = -u1[t];
+            if (K == 2) {
+                at[(ql + 1) * L + t] = -l2[t];
+                at[(qu + 1) * L + t] = -u2[t];
+            }
+            if (cyclic && !full) {
+                at[qz * L + t] = -d.cor.z0[row];
+                if (K == 2) at[(qz + 1) * L + t] = -d.cor.z1[row];
+            }
+        }
+    }
+    if (cyclic && full) {
+        // the solve of f - U c: its forward intermediate is y - (forward of U)
+        // c and its solution x - Z c, so a chunk's history changes by the
+        // former at the rows above it and its future by the latter at the rows
+        // below it
+        const double (*u)[2] = d.cor.u;
+        for (int c = 0; c < K; ++c) {
+            const std::vector<double> &z = c == 0 ? d.cor.z0 : d.cor.z1;
+            std::vector<double> zy(n);
+            for (int64_t i = 0; i < n; ++i) {
+                double v = 0.0;
+                if (i < K) v = r.s[i] * u[i][c];
+                if (i >= n - K) v += r.s[i] * u[4 - (n - i)][c];
+                if (i >= 1) v -= r.l1[i] * zy[i - 1];
+                if (K == 2 && i >= 2) v -= r.l2[i] * zy[i - 2];
+                zy[i] = v;
+            }
+            for (int64_t j = 0; j < P; ++j)
+                for (int e = 0; e < K; ++e) {
+                    if (j > 0) HZ[j * KK + e * K + c] = -zy[j * C - 1 - e];
+                    if (j < P - 1) FZ[j * KK + e * K + c] = -z[(j + 1) * C + e];
+                }
+            // chunk 0 takes U's first rows through the history it does not
+            // have: y_0 += h2 and y_1 += h1 (tri: y_0 += h1); the last chunk
+            // U's last rows through its future: x_{n-2} += f1, x_{n-1} += f2
+            // (tri: x_{n-1} += f1)
+            if (K == 1) {
+                HZ[0] = -r.s[0] * u[0][0];
+                FZ[P - 1] = -r.s[n - 1] * u[3][0];
+            } else {
+                HZ[0 * K + c] = -r.s[1] * u[1][c];
+                HZ[1 * K + c] = -r.s[0] * u[0][c];
+                const double d2 = -r.s[n - 2] * u[2][c];
+                FZ[(P - 1) * KK + 0 * K + c] = d2;
+                FZ[(P - 1) * KK + 1 * K + c] = -r.s[n - 1] * u[3][c] - r.l1[n - 1] * d2;
+            }
+        }
+        double *first = tab.data(), *last = tab.data() + (int64_t)(P - 1) * (C + 1);
+        if (K == 1) {
+            first[ql * L] = 1.0;
+            last[qu * L + C - 1] = 1.0;
+        } else {
+            first[ql * L] = 0.0;
+            first[(ql + 1) * L] = 1.0;
+            first[(ql + 1) * L + 1] = 1.0;
+            last[qu * L + C - 1] = 0.0;
+            last[(qu + 1) * L + C - 1] = 1.0;
+            last[(qu + 1) * L + C - 2] = 1.0;
         }
     }
     return tab;

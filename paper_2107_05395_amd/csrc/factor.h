@@ -29,6 +29,7 @@ struct Recurrence {
 struct Correction {
     std::vector<double> z0, z1;
     CyclicQ q{};
+    double u[4][2] = {};   // rows 0, 1, n-2, n-1 of U (tri: rows 0 and n-1, column 0)
 };
 
 struct Direction {
@@ -75,6 +76,9 @@ int lanes_for(int64_t n, int C);
 // Host table in the layout of internal.h (T = double or float), optionally
 // followed by nothing else; residual bands are built separately.
 std::vector<double> build_table(const Direction &d, int K, bool cyclic, int64_t n, int C, int P);
+// Table of the one-launch kernels (internal.h): build_table's layout and
+// values but for the periodic correction, in O(n) operations.
+std::vector<double> build_sweep_table(const Direction &d, int K, bool cyclic, int64_t n, int C, int P);
 std::vector<double> build_band_table(const Factor &f, int C, int P);
 
 }  // namespace bb

@@ -92,6 +92,27 @@ inline int64_t table_len(int K, bool cyclic, int C, int P)
     return (int64_t)num_arrays(K, cyclic) * P * (C + 1) + 3LL * P * K * K;
 }
 
+// Tables of the one-launch kernels (build_sweep_table): as above, except for
+// periodic matrices.  There the correction scalars are known from the scans,
+// before the passes over the rows:
+//   * full decompositions (P*C == n) apply them to the chunks' histories and
+//     futures alone, H_j += HZ_j c and F_j += FZ_j c, and need no z arrays: in
+//     place of x = y - Z c after the passes, the passes themselves run on the
+//     corrected right-hand side f - U c (U has entries in rows 0, 1, n-2 and
+//     n-1 only; chunk 0's history and the last chunk's future, otherwise
+//     unused, carry those).  Matrices HZ[P][K][K], FZ[P][K][K] follow G;
+//   * ragged ones keep the z arrays, and the end state of the last real chunk
+//     (its wE and Mf) is (y_{n-1}, y_{n-2}) instead of that of its padding.
+__host__ __device__ constexpr int sweep_arrays(int K, bool cyclic, bool full)
+{
+    return num_arrays(K, cyclic && !full);
+}
+
+inline int64_t sweep_table_len(int K, bool cyclic, bool full, int C, int P)
+{
+    return (int64_t)sweep_arrays(K, cyclic, full) * P * (C + 1) + (cyclic && full ? 5LL : 3LL) * P * K * K;
+}
+
 // Uniform arguments of a sweep launch.
 struct SweepGeom {
     int n;          // rows per system
@@ -111,11 +132,10 @@ struct SweepGeom {
 constexpr int kMaxLog2Q = 3;
 inline int max_log2q(int C, bool refine) { return (refine ? C > 32 : C > 64) ? 2 : 3; }
 
-// LDS elements of the exchange area of one split group: three phases
-// (forward scan: 2 per lane, backward scan: 2, periodic end values: 4).
-__host__ __device__ constexpr int64_t split_exchange_len(int log2Q) { return 8LL * kWave << log2Q; }
-// ... and of a fourth phase: rows 0, 1, n-2, n-1 of every (chunk, slot).
-__host__ __device__ constexpr int64_t split_ends_len(int log2Q) { return 4LL * kWave << log2Q; }
+// LDS elements of the exchange area of one split group: two phases (forward
+// scan: K per lane, backward scan: K).  A phase is written again only after
+// the barrier of the other, which every wave reaches with its reads done.
+__host__ __device__ constexpr int64_t split_exchange_len(int K, int log2Q) { return 2LL * K * kWave << log2Q; }
 
 // Tuning overrides of the automatic decomposition choices (measurement and
 // tests), process-wide, set through bb_set_tuning; -1 means automatic.

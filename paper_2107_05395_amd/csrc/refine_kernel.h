@@ -9,15 +9,31 @@
 namespace bb {
 namespace {
 
+// Waves per SIMD the kernel is held to: two with FP32 right-hand sides of
+// tridiagonal systems in 4-wave groups, whose 258 registers would leave one
+// (tri n = 512, m = 2^19: 1151 us at one wave, 793 at two).
+constexpr int refine_waves(int K, int C, int QL, size_t rhs_bytes)
+{
+    return (K == 1 && C == 64 && QL == 2 && rhs_bytes == 4) || QL == 3 ? 2 : 1;
+}
+
+// Steps of the group's scans per block: one for tridiagonal systems, whose
+// kernel has no registers to hold four at two waves per SIMD (n = 512,
+// m = 2^19, FP32 right-hand sides: 873 us with four, 781 with one); four for
+// pentadiagonal ones (n = 1024, m = 2^17: 690 us, 704 with one).
+template <int K>
+constexpr int kRefineSteps = K == 1 ? 1 : 4;
+
 // ---------------------------------------------------------------- refine
 // x0 = solve_f32(b); r = b - A x0 in double with the original bands;
 // x = x0 + solve_f32(r), stored as double.
-// QL > 0: split groups as in sweep_kernel; the exchange area holds the three
+// QL > 0: split groups as in sweep_kernel; the exchange area holds the two
 // phases of chunk_solve followed by rows 0, 1, C-2, C-1 of every chunk.
 // TB: type of the right-hand sides in memory -- double, or float when the
 // right-hand sides are FP32 data (promoted exactly for the residual).
 template <int K, int C, bool CYC, bool FULL, int QL, typename TB>
-__global__ __launch_bounds__((kWave << QL) > kMaxBlockThreads ? (kWave << QL) : kMaxBlockThreads)
+__global__ __launch_bounds__((kWave << QL) > kMaxBlockThreads ? (kWave << QL) : kMaxBlockThreads,
+                             refine_waves(K, C, QL, sizeof(TB)))
 void refine_kernel(
     const float *__restrict__ table, int64_t table_elems, const double *__restrict__ band_table,
     int64_t band_elems, CyclicQ cq, Corners cn, SweepGeom g, const TB *in, double *out)
@@ -51,7 +67,8 @@ void refine_kernel(
         float x0[C];
 #pragma unroll
         for (int t = 0; t < C; ++t) x0[t] = (float)b[t];
-        chunk_solve<float, K, C, CYC, (QL > 0)>(x0, lds, lg, g.n, exact, cq, xch);
+        chunk_solve<float, K, C, CYC, FULL, (QL > 0), FromLds<float>, false, kRefineSteps<K>>(
+            x0, lds, lg, g.n, cq, xch);
         __builtin_amdgcn_sched_barrier(0);
 
         // neighbours across the chunk boundaries (zero outside the matrix) and,
@@ -59,7 +76,7 @@ void refine_kernel(
         float xl1, xl2, xr1, xr2, r0 = 0.f, r1 = 0.f, rn2 = 0.f, rn1 = 0.f;
         if constexpr (QL > 0) {
             const int PS = lg.P * lg.S;
-            float *xd = xch + 8 * PS;   // [4][P*S]: rows 0, 1, C-2, C-1 of (chunk, slot)
+            float *xd = xch + 2 * K * PS;   // [4][P*S]: rows 0, 1, C-2, C-1 of (chunk, slot)
             const int me = lg.j * lg.S + lg.sl;
             xd[me] = x0[0];
             xd[PS + me] = x0[1];
@@ -135,7 +152,8 @@ void refine_kernel(
             dx[t] = (float)r;
         });
         __builtin_amdgcn_sched_barrier(0);
-        chunk_solve<float, K, C, CYC, (QL > 0)>(dx, lds, lg, g.n, exact, cq, xch);
+        chunk_solve<float, K, C, CYC, FULL, (QL > 0), FromLds<float>, false, kRefineSteps<K>>(
+            dx, lds, lg, g.n, cq, xch);
         if (kval)
             store_chunk_fn<C, FULL>([&](int t) { return (double)x0[t] + (double)dx[t]; }, out, row0,
                                     k, g.ld, g.n);
@@ -152,7 +170,7 @@ hipError_t refine_c(const void *table, int64_t table_elems, const double *band,
         if constexpr (C >= 32) {
             if (!is_full(g) || g.log2Q > max_log2q(C, true) || g.log2Q > g.log2P)
                 return hipErrorInvalidValue;
-            const size_t xl = (size_t)(split_exchange_len(g.log2Q) + (4LL * kWave << g.log2Q)) * sizeof(float);
+            const size_t xl = (size_t)(split_exchange_len(K, g.log2Q) + (4LL * kWave << g.log2Q)) * sizeof(float);
             if (g.log2Q == 1)
                 return launch_grid_split(refine_kernel<K, C, CYC, true, 1, TB>, lds + xl, g.groups, 2,
                                          stream, (const float *)table, table_elems, band,

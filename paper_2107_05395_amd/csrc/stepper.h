@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kMaxBlockThreads) void step_kernel(const double *__
             }
             rhs.template operator()<C, FULL>(c, h, lg.j, lg.j == lg.P - 1, opaque_v(g.n - row0), ls);
             __builtin_amdgcn_sched_barrier(0);
-            chunk_solve<double, K, C, CYC>(c, smem_d, lg, g.n, exact, cq);
+            chunk_solve<double, K, C, CYC, FULL>(c, smem_d, lg, g.n, cq);
             if (STATS && (step + 1) % st.every == 0) {
                 // chunks of a system: lanes j*S + sl of this wave, summed in chunk order
                 const double ss = chunk_sum_sq<C>(c);
@@ -149,6 +149,18 @@ __global__ __launch_bounds__(kMaxBlockThreads) void step_kernel(const double *__
     }
 }
 
+// Waves per SIMD a split kernel is held to.  Three, with 64-row chunks in 168
+// VGPRs, where the compiler gets there without spills (a workgroup of four
+// waves or fewer, at most two halo rows): a step waits at its barriers and
+// for its recurrences, and the other workgroups of the CU fill in.  The
+// Cahn-Hilliard kernel with the statistic, 2 VGPRs over: 2746 us at two
+// (n = 256, m = 2^18, 50 steps).
+constexpr int step_waves(int K, int C, int QL, bool scalar, int rows, int R)
+{
+    const bool three = C == 64 && QL <= 2 && R <= 2 && (scalar || (rows == 4 && K == 1));
+    return three ? 3 : QL == 3 ? 2 : 1;
+}
+
 // The same steps with a system group split over the Q = 2^QL waves of a
 // workgroup (chunks tile n exactly): wave q holds chunks q*P/Q ..
 // (q+1)*P/Q - 1 of S = 64Q/P systems, and every chunk-boundary value goes
@@ -158,8 +170,12 @@ __global__ __launch_bounds__(kMaxBlockThreads) void step_kernel(const double *__
 // coefficient row at the same time, so the coefficients come from the global
 // table through the scalar cache (no LDS staging, no LDS reads).  Otherwise
 // the table is staged in LDS ahead of the exchange area.
-template <class Rhs, int K, bool CYC, int C, int QL, bool SCALAR, bool STATS, bool TRAJ>
-__global__ __launch_bounds__((kWave << QL) > kMaxBlockThreads ? (kWave << QL) : kMaxBlockThreads)
+// ROWS: chunks per wave (2 or 4) of a group whose LDS coefficients go by row
+// broadcast, 0: plain LDS reads.
+template <class Rhs, int K, bool CYC, int C, int QL, bool SCALAR, bool STATS, bool TRAJ,
+          int ROWS = 0>
+__global__ __launch_bounds__((kWave << QL) > kMaxBlockThreads ? (kWave << QL) : kMaxBlockThreads,
+                             step_waves(K, C, QL, SCALAR, ROWS, Rhs::R))
 void step_kernel_split(const double *__restrict__ table, int64_t table_elems, CyclicQ cq,
                        SweepGeom g, Rhs rhs, int64_t steps, StepStats st, const double *in,
                        double *out)
@@ -169,7 +185,7 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
     extern __shared__ double smem_d[];
     const int64_t tl = SCALAR ? 0 : table_elems;
     double *xch = smem_d + tl;                              // chunk_solve phases
-    double *xd = xch + split_exchange_len(QL);              // [2R][P*S]: rows 0, C-1, 1, C-2, 2, C-3
+    double *xd = xch + split_exchange_len(K, QL);              // [2R][P*S]: rows 0, C-1, 1, C-2, 2, C-3
     double *xs = xd + ((2LL * R * kWave) << QL);            // [P*S]: sums of squares
     typename Src::ptr tab;
     if constexpr (SCALAR) {
@@ -182,8 +198,8 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
 
     // SCALAR: P == Q (the host checks log2P == QL), so the geometry is known
     // at compile time: S = 64, one chunk per wave
-    LaneGeom lg = lane_geom(SCALAR ? QL : g.log2P, QL);
-    if constexpr (SCALAR) lg.j = __builtin_amdgcn_readfirstlane(lg.j);   // the wave's chunk
+    LaneGeom lg = lane_geom(SCALAR ? QL : ROWS > 0 ? QL + ROWS / 2 : g.log2P, QL);
+    if constexpr (SCALAR) lg.j = lg.j0;   // the wave's chunk
     const int row0 = lg.j * C;
     const bool has_left = lg.j > 0, has_right = lg.j < lg.P - 1;
     const int PS = lg.P * lg.S;
@@ -236,7 +252,8 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
             }
             rhs.template operator()<C, true>(c, h, lg.j, !has_right, C, ls);
             __builtin_amdgcn_sched_barrier(0);
-            chunk_solve<double, K, C, CYC, true, Src>(c, tab, lg, g.n, 1, cq, xch);
+            chunk_solve<double, K, C, CYC, true, true, Src, (ROWS > 0), (SCALAR && QL < 2 ? 1 << QL : ROWS > 0 && K == 1 ? 8 : 4)>(
+                c, tab, lg, g.n, cq, xch);
             if (STATS && (step + 1) % st.every == 0) {
                 // chunks of a system through LDS, summed in chunk order, by
                 // wave 0 (it holds chunk 0: lanes 0 .. S-1 are the group)
@@ -263,10 +280,12 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
 }
 
 // LDS bytes of the split kernel beyond the staged table: the chunk_solve
-// exchange, 2R rows per (chunk, slot) and one sum of squares per (chunk, slot).
-constexpr size_t split_step_lds(int QL, int R)
+// exchange, 2R rows per (chunk, slot) and, for the statistic, one sum of squares
+// per (chunk, slot).
+constexpr size_t split_step_lds(int K, int QL, int R, bool stats)
 {
-    return (size_t)(split_exchange_len(QL) + ((2LL * R * kWave) << QL) + (kWave << QL)) * sizeof(double);
+    return (size_t)(split_exchange_len(K, QL) + ((2LL * R * kWave) << QL) + (stats ? kWave << QL : 0)) *
+           sizeof(double);
 }
 
 // Launch `steps` fused steps.  g.log2Q > 0 selects the split kernel (full
@@ -288,7 +307,7 @@ hipError_t launch_stepper(const double *table, int64_t table_elems, const Cyclic
         // one chunk per wave: 16-, 32- or 64-row chunks tiling n into at most 8
         if ((g.C != 16 && g.C != 32 && g.C != 64) || g.log2Q != g.log2P || g.log2Q > 3 || !is_full(g))
             return hipErrorInvalidValue;
-        const size_t xl = split_step_lds(g.log2Q, Rhs::R);
+        const size_t xl = split_step_lds(K, g.log2Q, Rhs::R, STATS);
 #define BB_SCALAR(CC)                                                                                    \
         case CC:                                                                                         \
             switch (g.log2Q) {                                                                           \
@@ -308,9 +327,15 @@ hipError_t launch_stepper(const double *table, int64_t table_elems, const Cyclic
     if (g.log2Q > 0) {
         // LDS table, group split over 2^log2Q waves: 32- and 64-row chunks
         if (g.log2Q > 3 || g.log2Q > g.log2P || !is_full(g)) return hipErrorInvalidValue;
-        const size_t xl = (size_t)table_elems * sizeof(double) + split_step_lds(g.log2Q, Rhs::R);
+        const size_t xl = (size_t)table_elems * sizeof(double) + split_step_lds(K, g.log2Q, Rhs::R, STATS);
 #define BB_SPLIT(CC)                                                                                     \
         case CC:                                                                                         \
+            if (CC == 64 && g.log2Q == 2 && g.log2P == 4)                                                \
+                return launch_grid_split(step_kernel_split<Rhs, K, CYC, CC, 2, false, STATS, TRAJ, 4>, xl, g.groups, 4, s, table, table_elems, q, g, rhs, steps, st, in, out); \
+            if (CC == 64 && g.log2Q == 3 && g.log2P == 4)                                                \
+                return launch_grid_split(step_kernel_split<Rhs, K, CYC, CC, 3, false, STATS, TRAJ, 2>, xl, g.groups, 8, s, table, table_elems, q, g, rhs, steps, st, in, out); \
+            if (g.log2Q == 3 && g.log2P == 5)                                                            \
+                return launch_grid_split(step_kernel_split<Rhs, K, CYC, CC, 3, false, STATS, TRAJ, 4>, xl, g.groups, 8, s, table, table_elems, q, g, rhs, steps, st, in, out); \
             switch (g.log2Q) {                                                                           \
             case 1: return launch_grid_split(step_kernel_split<Rhs, K, CYC, CC, 1, false, STATS, TRAJ>, xl, g.groups, 2, s, table, table_elems, q, g, rhs, steps, st, in, out); \
             case 2: return launch_grid_split(step_kernel_split<Rhs, K, CYC, CC, 2, false, STATS, TRAJ>, xl, g.groups, 4, s, table, table_elems, q, g, rhs, steps, st, in, out); \

@@ -16,7 +16,10 @@
 // from LDS (staged once per workgroup) or through the scalar cache.
 #pragma once
 
+#include <type_traits>
+
 #include "internal.h"
+#include "row_bcast.h"
 
 namespace bb {
 namespace {
@@ -120,9 +123,10 @@ __device__ __forceinline__ T pick(const T (&v)[C], int t)
     return r;
 }
 
-// Where this lane sits: chunk j (of P) of system slot sl (of S) in its group.
+// Where this lane sits: chunk j (of P) of system slot sl (of S) in its group;
+// its wave holds chunks j0 .. j0 + W - 1 (uniform).
 struct LaneGeom {
-    int j, sl, S, P;
+    int j, sl, S, P, j0, W;
 };
 
 // This lane's view of a coefficient table (layout in internal.h); Ptr is the
@@ -208,6 +212,169 @@ __device__ __forceinline__ void correction_scalars(const CyclicQ &cq, T r0, T r1
     }
 }
 
+// Matrices of the 16 chunks from distance d0 along a scan, lane l of a row:
+// chunk c0 + l.  With fewer than 16 chunks the other lanes read past or
+// before them, inside the workgroup's LDS, and their values are not used.
+template <typename T, int K, bool UP>
+__device__ __forceinline__ void row_mats(const T *lds_mats, const LaneGeom &lg, int d0, T (&m)[K * K])
+{
+    const int c0 = UP ? d0 : lg.P < 16 ? lg.P - 8 : lg.P - 16 - d0;
+    const int lane = threadIdx.x % kRowLanes;
+#pragma unroll
+    for (int q = 0; q < K * K; ++q) m[q] = lds_mats[(c0 + lane) * K * K + q];
+}
+
+// The scans of a split group.  Every lane walks the other chunks' boundary
+// states in the exchange area xa (component c of chunk i at
+// xa[c*P*S + i*S + slot]): state i = e_i + M_i state_{i-1} over the chunks
+// before (UP) or after its own, taking the state that enters its chunk.  The
+// chain's latency is what they cost, so everything four steps need is loaded
+// before them: the boundary states, and the chunk matrices, which are the
+// same for every lane -- held by the lanes of a row and taken by row
+// broadcast (ROWS), else read from LDS or through the scalar cache like the
+// coefficients.  With a load inside each
+// step the two scans took 6000 of the 13400 clocks of a step of one group at
+// 16 chunks.  The steps past the last chunk a wave needs run on clamped
+// loads and are not taken.
+// ENDS (periodic): every wave walks the first `steps` chunks of the chain and
+// also takes the state that leaves the last of them, (y1, y2).
+// BL: steps per block.
+template <typename T, int K, bool ROWS, bool UP, bool ENDS, int BL, typename MP>
+__device__ __forceinline__ void group_scan(const T *xa, MP mats, const LaneGeom &lg, int steps,
+                                           T &h1, T &h2, T &y1, T &y2)
+{
+    constexpr int KK = K * K;
+    static_assert(!ROWS || BL == 4 || (K == 1 && BL == 8), "steps of the row-broadcast chain");
+    const int PS = lg.P * lg.S;
+    // chunk at distance d along the chain: d, or P-1-d
+    const int mine = UP ? lg.j : lg.P - 1 - lg.j;
+    const int near = UP ? lg.j0 : lg.P - lg.j0 - lg.W;   // the wave's nearest chunk
+    const int far = near + lg.W - 1;                     // ... and its farthest
+    const int lim = ENDS && steps - 1 > far ? steps - 1 : far;   // last block runs to here
+    T a1 = T(0), a2 = T(0);
+    h1 = h2 = T(0);
+    auto chunk_at = [&](int d) { return UP ? d : lg.P - 1 - d; };
+    auto block = [&](auto lane0, int d0, const T (&m)[ROWS ? KK : BL * KK]) __attribute__((always_inline)) {
+        T e[BL], g[BL];
+#pragma unroll
+        for (int b = 0; b < BL; ++b) {
+            const int i = chunk_at(d0 + b < lg.P ? d0 + b : lg.P - 1);
+            e[b] = xa[i * lg.S + lg.sl];
+            g[b] = K == 2 ? xa[PS + i * lg.S + lg.sl] : T(0);
+        }
+        const T b1 = a1, b2 = a2;
+        if constexpr (ROWS) {
+            // four steps at a time; lanes hold the matrices by chunk number, so
+            // a block going down the chunks runs over its lanes from the top
+#pragma unroll
+            for (int b0 = 0; b0 < BL; b0 += 4) {
+                T e4[4], g4[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    e4[UP ? b : 3 - b] = e[b0 + b];
+                    g4[UP ? b : 3 - b] = g[b0 + b];
+                }
+                constexpr int L0 = decltype(lane0)::value;
+                if (b0 == 0)
+                    chain4<K, UP, L0>(e4, g4, m, a1, a2);
+                else
+                    chain4<K, UP, UP ? (L0 + 4) % 16 : (L0 + 12) % 16>(e4, g4, m, a1, a2);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    e[b0 + b] = e4[UP ? b : 3 - b];
+                    g[b0 + b] = g4[UP ? b : 3 - b];
+                }
+                a1 = e[b0 + 3];
+                a2 = g[b0 + 3];
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < BL; ++b) {
+                affine<T, K>(m + b * KK, a1, a2, e[b], g[b]);
+                e[b] = a1;
+                g[b] = a2;
+            }
+        }
+        a1 = e[BL - 1];
+        a2 = g[BL - 1];
+        // the state entering the lane's chunk: before step `mine`
+        if (near < d0 + BL && far >= d0) {
+#pragma unroll
+            for (int b = 0; b < BL; ++b) {
+                const bool me = mine == d0 + b;
+                h1 = me ? (b == 0 ? b1 : e[b == 0 ? 0 : b - 1]) : h1;
+                if constexpr (K == 2) h2 = me ? (b == 0 ? b2 : g[b == 0 ? 0 : b - 1]) : h2;
+            }
+        }
+        if (ENDS && steps - 1 >= d0 && steps - 1 < d0 + BL) {
+#pragma unroll
+            for (int b = 0; b < BL; ++b) {
+                y1 = steps - 1 == d0 + b ? e[b] : y1;
+                if constexpr (K == 2) y2 = steps - 1 == d0 + b ? g[b] : y2;
+            }
+        }
+    };
+    if constexpr (ROWS) {
+        for (int d0 = 0; d0 <= lim; d0 += 16) {
+            T m[KK];
+            row_mats<T, K, UP>(mats, lg, d0, m);
+            // lanes of the block's chunks: from the row's low end going up,
+            // from its high end going down (from lane 7 with fewer than 16
+            // chunks)
+            auto at = [&](auto i) {
+                constexpr int o = decltype(i)::value;
+                if (d0 + o > lim) return;
+                if (!UP && lg.P < 16)
+                    block(std::integral_constant<int, (o < 8 ? 4 - o : 0)>{}, d0 + o, m);
+                else
+                    block(std::integral_constant<int, UP ? o : 12 - o>{}, d0 + o, m);
+            };
+            at(std::integral_constant<int, 0>{});
+            if constexpr (BL == 4) at(std::integral_constant<int, 4>{});
+            at(std::integral_constant<int, 8>{});
+            if constexpr (BL == 4) at(std::integral_constant<int, 12>{});
+        }
+    } else {
+        for (int d0 = 0; d0 <= lim; d0 += BL) {
+            T m[BL * KK];
+#pragma unroll
+            for (int b = 0; b < BL; ++b)
+#pragma unroll
+                for (int q = 0; q < KK; ++q)
+                    m[b * KK + q] = mats[chunk_at(d0 + b < lg.P ? d0 + b : lg.P - 1) * KK + q];
+            block(std::integral_constant<int, 0>{}, d0, m);
+        }
+    }
+}
+
+// Coefficient array q of this lane's chunk for the row-broadcast passes.
+template <int C>
+__device__ __forceinline__ const double *row_base(const double *tab, const LaneGeom &lg, int q)
+{
+    return tab + q * lg.P * (C + 1) + lg.j * (C + 1) + (int)(threadIdx.x % kRowLanes);
+}
+
+// x += z0 c0 (+ z1 c1) on this lane's chunk, row-broadcast coefficients
+template <int K, int C>
+__device__ __forceinline__ void rows_correct(double (&v)[C], const double *tab, const LaneGeom &lg,
+                                             double c0, double c1)
+{
+    constexpr int qz = 4 * K + 1;
+    const RowCoef<C> z0 = row_coef<C>(row_base<C>(tab, lg, qz));
+    if constexpr (K == 1) {
+        blocks8_up<C>([&](auto t) {
+            constexpr int t_ = decltype(t)::value;
+            rows8_correct<t_, C>(v, c0, z0.r[t_ / 16]);
+        });
+    } else {
+        const RowCoef<C> z1 = row_coef<C>(row_base<C>(tab, lg, qz + 1));
+        blocks8_up<C>([&](auto t) {
+            constexpr int t_ = decltype(t)::value;
+            rows8_correct<t_, C>(v, c0, c1, z0.r[t_ / 16], z1.r[t_ / 16]);
+        });
+    }
+}
+
 // Solve this lane's chunk in place: v holds the right-hand side rows on entry
 // and the solution rows on exit.  All 64 lanes of the wave must call it
 // together (the scans shuffle across the wave).
@@ -219,24 +386,57 @@ __device__ __forceinline__ void correction_scalars(const CyclicQ &cq, T r0, T r1
 //   scans:  history H_j (prefix over chunks, H_{i+1} = e_i + Mf_i H_i), then
 //           S_j = o_j + G_j H_j and the future F_j (suffix, F_{i-1} = S_i + Mb_i F_i);
 //   pass 2: forward recurrence from H_j, writing y;
-//   pass 3: backward recurrence from F_j, writing x (periodic correction fused
-//           when the chunks tile n exactly, else applied afterwards).
+//   pass 3: backward recurrence from F_j, writing x.
+// Periodic: the correction scalars follow from the scans; a full
+// decomposition (FULL) puts them into H_j and F_j, a ragged one adds the
+// correction's rows in pass 3 (internal.h, build_sweep_table).
 // Each pass re-derives its table pointers (LDS or scalar) from an opaque base
 // so the compiler re-reads coefficients instead of keeping C of them live
 // across passes.
 //
 // SPLIT: the group spans several waves of the workgroup; boundary states go
-// through the exchange area xch (split_exchange_len elements, plus
-// split_ends_len when the chunks do not tile n exactly in a periodic solve)
-// with workgroup barriers, so every wave of the workgroup must call it the
-// same number of times.
-template <typename T, int K, int C, bool CYC, bool SPLIT = false, typename Src = FromLds<T>>
+// through the exchange area xch (split_exchange_len elements) with workgroup
+// barriers, so every wave of the workgroup must call it the same number of
+// times.
+// ROWS: the passes take their coefficients by row broadcast (row_bcast.h):
+// double, table in LDS, S a multiple of 16 so that a 16-lane row works on one
+// chunk.
+// BL: steps per block of the group's scans.
+template <typename T, int K, int C, bool CYC, bool FULL, bool SPLIT = false,
+          typename Src = FromLds<T>, bool ROWS = false, int BL = 4>
 __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, const LaneGeom &lg,
-                                            int n, int exact, const CyclicQ &cq, T *xch = nullptr)
+                                            int n, const CyclicQ &cq, T *xch = nullptr)
 {
+    static_assert(!ROWS || (std::is_same<T, double>::value && std::is_same<Src, FromLds<T>>::value &&
+                            C % kRowLanes == 0),
+                  "row-broadcast coefficients: double, LDS table, 16-row blocks");
+    // array indices of the table (internal.h)
+    constexpr int qE = 0, qW = K, qs = 2 * K, ql = 2 * K + 1, qu = 3 * K + 1;
+    constexpr bool ZROWS = CYC && !FULL;   // the table has z arrays
+    const int real = FULL ? lg.P : (n - 1) / C + 1;   // real chunks
+    // the chunk matrices, for the scans of a split group
+    const auto mats = tab + sweep_arrays(K, CYC, FULL) * lg.P * (C + 1);
     T e1 = T(0), e2 = T(0), o1 = T(0), o2 = T(0);
-    {
-        const auto tb = lane_table<T, K, C, CYC>(Src::base(tab), lg.P, lg.j);
+    if constexpr (ROWS) {
+        const double *t0 = Src::base(tab);
+        const RowCoef<C> we1 = row_coef<C>(row_base<C>(t0, lg, qE));
+        const RowCoef<C> ws1 = row_coef<C>(row_base<C>(t0, lg, qW));
+        if constexpr (K == 1) {
+            blocks8_up<C>([&](auto t) {
+                constexpr int t_ = decltype(t)::value;
+                rows8_ends<t_, C>(v, e1, o1, we1.r[t_ / 16], ws1.r[t_ / 16]);
+            });
+        } else {
+            const RowCoef<C> we2 = row_coef<C>(row_base<C>(t0, lg, qE + 1));
+            const RowCoef<C> ws2 = row_coef<C>(row_base<C>(t0, lg, qW + 1));
+            blocks8_up<C>([&](auto t) {
+                constexpr int t_ = decltype(t)::value;
+                rows8_ends<t_, C>(v, e1, o1, e2, o2, we1.r[t_ / 16], ws1.r[t_ / 16], we2.r[t_ / 16],
+                                  ws2.r[t_ / 16]);
+            });
+        }
+    } else {
+        const auto tb = lane_table<T, K, C, ZROWS>(Src::base(tab), lg.P, lg.j);
         rows_up<C>([&](int t) {
             e1 = fma(tb.wE1[t], v[t], e1);
             o1 = fma(tb.wS1[t], v[t], o1);
@@ -248,21 +448,20 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
     }
     __builtin_amdgcn_sched_barrier(0);
     // history of this chunk: H_j = true (y_{start-1}, y_{start-2})
-    const auto tb = lane_table<T, K, C, CYC>(Src::base(tab), lg.P, lg.j);
+    const auto tb = lane_table<T, K, C, ZROWS>(Src::base(tab), lg.P, lg.j);
     T h1 = T(0), h2 = T(0);
+    // periodic: y_{n-1} and y_{n-2} of the last real chunk's forward pass, x_0 and x_1
+    T y1e = T(0), y2e = T(0), x0e = T(0), x1e = T(0);
     // exchange area: structure of arrays of P*S entries, (chunk, slot) at
     // chunk*S + slot, so a wave's accesses are consecutive words
     const int me = lg.j * lg.S + lg.sl;
     const int PS = lg.P * lg.S;
     if constexpr (SPLIT) {
-        T *xa = xch;   // [2][P*S]
+        T *xa = xch;   // [K][P*S]
         xa[me] = e1;
-        xa[PS + me] = e2;
+        if constexpr (K == 2) xa[PS + me] = e2;
         __syncthreads();
-        for (int i = 0; i < lg.j; ++i) {
-            const int src = i * lg.S + lg.sl;
-            affine<T, K>(tb.Mf + i * K * K, h1, h2, xa[src], xa[PS + src]);
-        }
+        group_scan<T, K, ROWS, true, CYC, BL>(xa, mats, lg, real, h1, h2, y1e, y2e);
     } else {
         for (int i = 0; i < lg.P; ++i) {
             const int src = i * lg.S + lg.sl;
@@ -285,14 +484,11 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
     // future of this chunk: F_j = true (x_{end+1}, x_{end+2})
     T f1 = T(0), f2 = T(0);
     if constexpr (SPLIT) {
-        T *xb = xch + 2 * PS;   // [2][P*S]
+        T *xb = xch + K * PS;   // [K][P*S]
         xb[me] = s1;
-        xb[PS + me] = s2;
+        if constexpr (K == 2) xb[PS + me] = s2;
         __syncthreads();
-        for (int i = lg.P - 1; i > lg.j; --i) {
-            const int src = i * lg.S + lg.sl;
-            affine<T, K>(tb.Mb + i * K * K, f1, f2, xb[src], xb[PS + src]);
-        }
+        group_scan<T, K, ROWS, false, CYC, BL>(xb, mats + lg.P * K * K, lg, lg.P, f1, f2, x0e, x1e);
     } else {
         for (int i = lg.P - 1; i >= 0; --i) {
             const int src = i * lg.S + lg.sl;
@@ -301,49 +497,59 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
             if (i > lg.j) affine<T, K>(tb.Mb + i * K * K, f1, f2, a1, a2);
         }
     }
-    // periodic correction x = y - Z s, s = Q (y_0..y_{K-1}, y_{n-K}..y_{n-1}), from
-    // the scan results when the chunks tile n exactly
+    // periodic correction scalars c = Q (x_0, x_1, x_{n-2}, x_{n-1}) of the
+    // solution without it (the last chunk's future is zero, so x_{n-1} =
+    // y_{n-1} and x_{n-2} = y_{n-2} - u1 y_{n-1})
     T c0 = T(0), c1 = T(0);
     if constexpr (CYC) {
-        if (exact) {
-            // rows 0, 1: start state of chunk 0 = S_0 + Mb_0 F_0
-            T x0 = s1, x1 = s2;
-            {
-                T g1 = f1, g2 = f2;
-                affine<T, K>(tb.Mb + lg.j * K * K, g1, g2, s1, s2);
-                x0 = g1;
-                x1 = g2;
-            }
-            // rows n-1, n-2: the last real chunk's true forward end state (its
-            // future is zero, so x_{n-1} = y_{n-1}, x_{n-2} = y_{n-2} - u1 y_{n-1})
-            T y1 = h1, y2 = h2;
+        if constexpr (!SPLIT) {
+            T g1 = f1, g2 = f2, y1 = h1, y2 = h2;
+            affine<T, K>(tb.Mb + lg.j * K * K, g1, g2, s1, s2);
             affine<T, K>(tb.Mf + lg.j * K * K, y1, y2, e1, e2);
-            const int last = (n / C - 1) * lg.S + lg.sl;
-            T r0, r1, rn1, rn2;
-            if constexpr (SPLIT) {
-                T *xc = xch + 4 * PS;   // [4][P*S]
-                xc[me] = x0;
-                xc[PS + me] = x1;
-                xc[2 * PS + me] = y1;
-                xc[3 * PS + me] = y2;
-                __syncthreads();
-                r0 = xc[lg.sl];
-                r1 = xc[PS + lg.sl];
-                rn1 = xc[2 * PS + last];
-                rn2 = (K == 2) ? fma(T(cq.u1_nm2), rn1, xc[3 * PS + last]) : T(0);
+            const int last = (real - 1) * lg.S + lg.sl;
+            x0e = shfl(g1, lg.sl);
+            x1e = (K == 2) ? shfl(g2, lg.sl) : T(0);
+            y1e = shfl(y1, last);
+            y2e = (K == 2) ? shfl(y2, last) : T(0);
+        }
+        const T xn2 = (K == 2) ? fma(T(cq.u1_nm2), y1e, y2e) : T(0);
+        correction_scalars<T, K>(cq, x0e, x1e, xn2, y1e, c0, c1);
+        if constexpr (FULL) {
+            const auto HZ = tb.Mf + (3 * lg.P + lg.j) * K * K, FZ = tb.Mf + (4 * lg.P + lg.j) * K * K;
+            if constexpr (K == 1) {
+                h1 = fma(HZ[0], c0, h1);
+                f1 = fma(FZ[0], c0, f1);
             } else {
-                r0 = shfl(x0, lg.sl);
-                r1 = (K == 2) ? shfl(x1, lg.sl) : T(0);
-                rn1 = shfl(y1, last);
-                rn2 = (K == 2) ? fma(T(cq.u1_nm2), rn1, shfl(y2, last)) : T(0);
+                h1 = fma(HZ[1], c1, fma(HZ[0], c0, h1));
+                h2 = fma(HZ[3], c1, fma(HZ[2], c0, h2));
+                f1 = fma(FZ[1], c1, fma(FZ[0], c0, f1));
+                f2 = fma(FZ[3], c1, fma(FZ[2], c0, f2));
             }
-            correction_scalars<T, K>(cq, r0, r1, rn2, rn1, c0, c1);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
     // pass 2: forward recurrence from the true history
-    {
-        const auto tp = lane_table<T, K, C, CYC>(Src::base(tab), lg.P, lg.j);
+    if constexpr (ROWS) {
+        const double *t0 = Src::base(tab);
+        const RowCoef<C> cs = row_coef<C>(row_base<C>(t0, lg, qs));
+        const RowCoef<C> l1 = row_coef<C>(row_base<C>(t0, lg, ql));
+        if constexpr (K == 1) {
+            blocks8_up<C>([&](auto t) {
+                constexpr int t_ = decltype(t)::value;
+                const double y1 = t_ == 0 ? h1 : v[t_ == 0 ? 0 : t_ - 1];
+                rows8_forward<t_, C>(v, y1, cs.r[t_ / 16], l1.r[t_ / 16]);
+            });
+        } else {
+            const RowCoef<C> l2 = row_coef<C>(row_base<C>(t0, lg, ql + 1));
+            blocks8_up<C>([&](auto t) {
+                constexpr int t_ = decltype(t)::value;
+                const double y1 = t_ == 0 ? h1 : v[t_ == 0 ? 0 : t_ - 1];
+                const double y2 = t_ == 0 ? h2 : v[t_ == 0 ? 0 : t_ - 2];
+                rows8_forward<t_, C>(v, y1, y2, cs.r[t_ / 16], l1.r[t_ / 16], l2.r[t_ / 16]);
+            });
+        }
+    } else {
+        const auto tp = lane_table<T, K, C, ZROWS>(Src::base(tab), lg.P, lg.j);
         T y1 = h1, y2 = h2;
         rows_up<C>([&](int t) {
             T y = tp.s[t] * v[t];
@@ -355,9 +561,28 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
         });
     }
     __builtin_amdgcn_sched_barrier(0);
-    // pass 3: backward recurrence from the true future (+ fused periodic correction)
-    {
-        const auto tp = lane_table<T, K, C, CYC>(Src::base(tab), lg.P, lg.j);
+    // pass 3: backward recurrence from the true future (+ correction rows, ragged periodic)
+    if constexpr (ROWS) {
+        const double *t0 = Src::base(tab);
+        const RowCoef<C> u1 = row_coef<C>(row_base<C>(t0, lg, qu));
+        if constexpr (K == 1) {
+            blocks8_down<C>([&](auto t) {
+                constexpr int t_ = decltype(t)::value;
+                const double x1 = t_ + 8 == C ? f1 : v[t_ + 8 == C ? 0 : t_ + 8];
+                rows8_backward<t_, C>(v, x1, u1.r[t_ / 16]);
+            });
+        } else {
+            const RowCoef<C> u2 = row_coef<C>(row_base<C>(t0, lg, qu + 1));
+            blocks8_down<C>([&](auto t) {
+                constexpr int t_ = decltype(t)::value;
+                const double x1 = t_ + 8 == C ? f1 : v[t_ + 8 == C ? 0 : t_ + 8];
+                const double x2 = t_ + 8 == C ? f2 : v[t_ + 8 == C ? 0 : t_ + 9];
+                rows8_backward<t_, C>(v, x1, x2, u1.r[t_ / 16], u2.r[t_ / 16]);
+            });
+        }
+        if constexpr (ZROWS) rows_correct<K, C>(v, t0, lg, c0, c1);
+    } else {
+        const auto tp = lane_table<T, K, C, ZROWS>(Src::base(tab), lg.P, lg.j);
         T x1 = f1, x2 = f2;
         rows_down<C>([&](int t) {
             T x = v[t];
@@ -365,41 +590,12 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
             x = fma(tp.u1[t], x1, x);
             x2 = x1;
             x1 = x;
-            if constexpr (CYC) {
+            if constexpr (ZROWS) {
                 x = fma(tp.z0[t], c0, x);
                 if constexpr (K == 2) x = fma(tp.z1[t], c1, x);
             }
             v[t] = x;
         });
-    }
-    if constexpr (CYC) {
-        if (!exact) {
-            __builtin_amdgcn_sched_barrier(0);
-            T r0, r1, rn2, rn1;
-            if constexpr (SPLIT) {
-                // rows 0, 1 (chunk 0) and n-2, n-1 (wherever they sit) through
-                // the fourth phase of the exchange area
-                T *xd = xch + 8 * PS;   // [4][P*S]
-                xd[me] = v[0];
-                xd[PS + me] = v[1];
-                xd[2 * PS + me] = pick(v, (n - 2) % C);
-                xd[3 * PS + me] = pick(v, (n - 1) % C);
-                __syncthreads();
-                r0 = xd[lg.sl];
-                r1 = (K == 2) ? xd[PS + lg.sl] : T(0);
-                rn2 = (K == 2) ? xd[2 * PS + ((n - 2) / C) * lg.S + lg.sl] : T(0);
-                rn1 = xd[3 * PS + ((n - 1) / C) * lg.S + lg.sl];
-            } else {
-                gather_ends<T, K, C>(v, lg, n, exact, r0, r1, rn2, rn1);
-            }
-            correction_scalars<T, K>(cq, r0, r1, rn2, rn1, c0, c1);
-            const auto tp = lane_table<T, K, C, CYC>(Src::base(tab), lg.P, lg.j);
-            rows_up<C>([&](int t) {
-                T x = fma(tp.z0[t], c0, v[t]);
-                if constexpr (K == 2) x = fma(tp.z1[t], c1, x);
-                v[t] = x;
-            });
-        }
     }
 }
 
@@ -481,10 +677,14 @@ __device__ __forceinline__ void load_chunk(T (&v)[C], const T *base, int row0, i
         const T *p = base + (int64_t)(row0 < n ? row0 : n - 1) * ld + k;
 #pragma unroll
         for (int t = 0; t < C; ++t) {
-            const T x = *p;
-            v[t] = t < nv ? x : T(0);
+            v[t] = *p;
             p += (t + 1 < nv) ? ld : 0;
         }
+        // all loads in flight before the first is looked at: left to itself the
+        // compiler may wait for each in turn
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < C; ++t) v[t] = t < nv ? v[t] : T(0);
     }
 }
 
@@ -548,6 +748,8 @@ __device__ __forceinline__ LaneGeom lane_geom(int log2P, int log2Q = 0)
     const int q = (threadIdx.x / kWave) & ((1 << log2Q) - 1);
     lg.j = (q << lw) + (lane >> (6 - lw));
     lg.sl = lane & (lg.S - 1);
+    lg.j0 = __builtin_amdgcn_readfirstlane(q << lw);
+    lg.W = 1 << lw;
     return lg;
 }
 

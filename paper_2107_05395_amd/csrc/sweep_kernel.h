@@ -18,7 +18,9 @@ namespace {
 // the same group index, so the exchange barriers are reached uniformly.
 // TI: type of the right-hand sides in memory (T, or float read into double
 // sweeps: FP32 data solved in FP64, exact promotion).
-template <typename T, int K, int C, bool CYC, bool FULL, int QL, typename TI = T>
+// ROWS: coefficients by row broadcast (split groups of double sweeps with
+// 64-row chunks and at least 16 systems per chunk).
+template <typename T, int K, int C, bool CYC, bool FULL, int QL, typename TI = T, bool ROWS = false>
 __global__ __launch_bounds__((kWave << QL) > kMaxBlockThreads ? (kWave << QL) : kMaxBlockThreads)
 void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, SweepGeom g,
                   const TI *in, T *out)
@@ -31,23 +33,43 @@ void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, 
 
     const LaneGeom lg = lane_geom(g.log2P, QL);
     const int row0 = lg.j * C;
+    // ragged: only the waves that hold the last real chunk or padding take the
+    // loads and stores with a predicate and a pointer select per row
+    const bool all_real = FULL || (QL > 0 && (lg.j0 + lg.W) * C <= g.n);
     const GroupRange gr = group_range(g.groups, QL, g.linear);
     for (int64_t b = gr.first; b < gr.end; b += gr.stride) {
         const int64_t grp = begin_block(gr, b, g.lockstep);
         if (grp >= g.groups) continue;
         const int64_t k = grp * lg.S + lg.sl;
         const bool kval = k < g.m;
+        const int64_t kk = kval ? k : g.m - 1;
         T v[C];
         if constexpr (std::is_same<TI, T>::value) {
-            load_chunk<T, C, FULL>(v, in, row0, kval ? k : g.m - 1, g.ld, g.n);
+            if (all_real)
+                load_chunk<T, C, true>(v, in, row0, kk, g.ld, g.n);
+            else
+                load_chunk<T, C, false>(v, in, row0, kk, g.ld, g.n);
         } else {
             TI w[C];
-            load_chunk<TI, C, FULL>(w, in, row0, kval ? k : g.m - 1, g.ld, g.n);
+            if (all_real)
+                load_chunk<TI, C, true>(w, in, row0, kk, g.ld, g.n);
+            else
+                load_chunk<TI, C, false>(w, in, row0, kk, g.ld, g.n);
 #pragma unroll
             for (int t = 0; t < C; ++t) v[t] = (T)w[t];
         }
-        chunk_solve<T, K, C, CYC, (QL > 0)>(v, lds, lg, g.n, FULL || g.exact, cq, xch);
-        if (kval) store_chunk<T, C, FULL>(v, out, row0, k, g.ld, g.n);
+        // ragged: every load waited for here, on both paths above, so that none
+        // is pending in the compiler's books when the loop comes round; it
+        // would hold the next group's loads until this group's stores are done
+        // (tri n = 1000, m = 2^16: 234 against 390 us)
+        if constexpr (!FULL) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+        chunk_solve<T, K, C, CYC, FULL, (QL > 0), FromLds<T>, ROWS>(v, lds, lg, g.n, cq, xch);
+        if (kval) {
+            if (all_real)
+                store_chunk<T, C, true>(v, out, row0, k, g.ld, g.n);
+            else
+                store_chunk<T, C, false>(v, out, row0, k, g.ld, g.n);
+        }
     }
 }
 
@@ -56,7 +78,21 @@ hipError_t sweep_split(const void *table, int64_t table_elems, const CyclicQ &q,
                        const SweepGeom &g, const void *in, void *out, hipStream_t stream)
 {
     const size_t lds =
-        (size_t)(table_elems + split_exchange_len(QL) + (CYC ? split_ends_len(QL) : 0)) * sizeof(T);
+        (size_t)(table_elems + split_exchange_len(K, QL)) * sizeof(T);
+    // four chunks a wave at most: 16 systems or more per chunk, so that a
+    // 16-lane row works on one chunk (tri n = 512, m = 2^20: 1741 us with LDS
+    // reads, 1724 by row broadcast: a solve waits for HBM; the fused steppers,
+    // bound by the reads, gain a factor of two)
+    if constexpr (std::is_same<T, double>::value && C == 64 && QL >= 2) {
+        if (g.log2P - QL <= 2)
+            return is_full(g)
+                       ? launch_grid_split(sweep_kernel<T, K, C, CYC, true, QL, TI, true>, lds,
+                                           g.groups, 1 << QL, stream, (const T *)table, table_elems,
+                                           q, g, (const TI *)in, (T *)out)
+                       : launch_grid_split(sweep_kernel<T, K, C, CYC, false, QL, TI, true>, lds,
+                                           g.groups, 1 << QL, stream, (const T *)table, table_elems,
+                                           q, g, (const TI *)in, (T *)out);
+    }
     if (is_full(g))
         return launch_grid_split(sweep_kernel<T, K, C, CYC, true, QL, TI>, lds, g.groups, 1 << QL,
                                  stream, (const T *)table, table_elems, q, g, (const TI *)in,
