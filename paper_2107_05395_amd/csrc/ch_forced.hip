@@ -14,30 +14,52 @@ namespace {
 
 __device__ __forceinline__ double nl3(double c) { return fma(c * c, c, -c); }
 
-// dx times the one-sided WENO5 derivative from the five one-sided
-// differences v1..v5 ordered from the far upwind end (Jiang and Peng): three
-// third-order candidates blended with weights 0.1, 0.6, 0.3 over
-// (smoothness + eps)^2, eps = 1e-6 max v_q^2 + 1e-99.
-__device__ __forceinline__ double weno5(double v1, double v2, double v3, double v4, double v5)
+// N / S for S at least about 1 and far from overflow (or NaN): the reciprocal
+// to about 24 bits, two Newton steps, the quotient and its remainder's
+// correction (the IEEE division's scaling and fix-up of its exceptional
+// operands left out: 8 instructions instead of 11 to 13).
+__device__ __forceinline__ double divide_scaled(double N, double S)
 {
-    const double p1 = fma(v1, 1.0 / 3.0, fma(v2, -7.0 / 6.0, v3 * (11.0 / 6.0)));
-    const double p2 = fma(v2, -1.0 / 6.0, fma(v3, 5.0 / 6.0, v4 * (1.0 / 3.0)));
-    const double p3 = fma(v3, 1.0 / 3.0, fma(v4, 5.0 / 6.0, v5 * (-1.0 / 6.0)));
-    const double a = v1 - 2.0 * v2 + v3, b = v1 - 4.0 * v2 + 3.0 * v3;
-    const double c = v2 - 2.0 * v3 + v4, d = v2 - v4;
-    const double e = v3 - 2.0 * v4 + v5, g = 3.0 * v3 - 4.0 * v4 + v5;
-    const double s1 = fma(13.0 / 12.0, a * a, 0.25 * b * b);
-    const double s2 = fma(13.0 / 12.0, c * c, 0.25 * d * d);
-    const double s3 = fma(13.0 / 12.0, e * e, 0.25 * g * g);
-    const double vm = fmax(fmax(fmax(v1 * v1, v2 * v2), fmax(v3 * v3, v4 * v4)), v5 * v5);
-    const double eps = fma(1e-6, vm, 1e-99);
-    const double t1 = s1 + eps, t2 = s2 + eps, t3 = s3 + eps;
-    // 1/t_k from one division: t_k >= 1e-99, so t1 t2 t3 >= 1e-297 stays a
-    // normal double (and below 1e8 for differences of O(1) states)
-    const double inv = 1.0 / (t1 * t2 * t3);
-    const double r1 = t2 * t3 * inv, r2 = t1 * t3 * inv, r3 = t1 * t2 * inv;
-    const double w1 = 0.1 * r1 * r1, w2 = 0.6 * r2 * r2, w3 = 0.3 * r3 * r3;
-    return fma(w1, p1, fma(w2, p2, w3 * p3)) / (w1 + w2 + w3);
+    double r = __builtin_amdgcn_rcp(S);
+    r = fma(r, fma(-S, r, 1.0), r);
+    r = fma(r, fma(-S, r, 1.0), r);
+    const double q = N * r;
+    return fma(fma(-S, q, N), r, q);
+}
+
+// The five one-sided differences v1..v5 of the WENO5 scheme (Jiang and Peng;
+// three third-order candidates blended with weights 0.1, 0.6, 0.3 over
+// (smoothness + eps)^2, eps = 1e-6 max v_q^2 + 1e-99), ordered from the far
+// upwind end, enter through the second differences
+//   a = v2 - v1, b = v3 - v2, c = v4 - v3, d = v5 - v4:
+// the candidates are v3 + (5b - 2a)/6, v3 + (b + 2c)/6 and v3 + (4c - d)/6, and
+// four times the smoothness measures 13/3 (b - a)^2 + (3b - a)^2,
+// 13/3 (c - b)^2 + (b + c)^2 and 13/3 (d - c)^2 + (d - 3c)^2.  From row to row
+// these differences carry over, and for the other upwind side they are the
+// same numbers mirrored and negated, so a row selects four of them instead of
+// five differences of each side.  Returns dx times the derivative less v3.
+// The weights gamma_k / t_k^2 times (t1 t2 t3)^2 need no division; the common
+// scale 2^-e, e the exponent of eps, keeps the products in range (t_k is
+// between eps and about 4e7 eps), states of any magnitude included.
+__device__ __forceinline__ double weno5_rest(double a, double b, double c, double d, double vmax2)
+{
+    const double eps4 = fma(4e-6, vmax2, 4e-99);
+    const double e1 = b - a, e2 = c - b, e3 = d - c;
+    const double g1 = fma(3.0, b, -a), g2 = b + c, g3 = fma(-3.0, c, d);
+    constexpr double k = 13.0 / 3.0;
+    double t1 = fma(k * e1, e1, fma(g1, g1, eps4));
+    double t2 = fma(k * e2, e2, fma(g2, g2, eps4));
+    double t3 = fma(k * e3, e3, fma(g3, g3, eps4));
+    const int e = -__builtin_amdgcn_frexp_exp(eps4);
+    t1 = __builtin_ldexp(t1, e);
+    t2 = __builtin_ldexp(t2, e);
+    t3 = __builtin_ldexp(t3, e);
+    const double r1 = t2 * t3, r2 = t1 * t3, r3 = t1 * t2;
+    const double w1 = r1 * r1, w2 = r2 * r2, w3 = r3 * r3;
+    // weights 1 : 6 : 3; six times their sum
+    const double S = fma(6.0, w1, fma(36.0, w2, 18.0 * w3));
+    const double N = fma(w1, fma(5.0, b, -2.0 * a), fma(w2, fma(12.0, c, 6.0 * b), w3 * fma(12.0, c, -3.0 * d)));
+    return divide_scaled(N, S);
 }
 
 // f_i = C_i + alpha (N_{i-1} - 2 N_i + N_{i+1}) + beta W_i(C) + amp cos(kdx i),
@@ -47,6 +69,10 @@ __device__ __forceinline__ double weno5(double v1, double v2, double v3, double 
 // term dt v dC/deta with the WENO derivative W/dx gives beta = dt v / dx, the
 // forcing dt f0 k cos(k eta) at eta_i = i dx gives amp = dt f0 k and
 // kdx = k dx.
+// Bound by FP64 issue: 78 vector instructions a row (about 170 with five
+// differences of each side formed and selected per row and two divisions),
+// 92 with the solve; n = 512, m = 2^16: 131 -> 99 us a step, of 86 at one
+// instruction per 4 clocks.
 struct ForcedChRhs {
     static constexpr int R = 3;
     double alpha, dt, dx;
@@ -87,9 +113,9 @@ struct ForcedChRhs {
                 q3 = h.e2;
             }
         }
-        // row t + d of the chunk (d = 1..3) before this step
-        auto ahead = [&](int t, int d) -> double {
-            const int u = t + d;
+        // row t + 3 of the chunk before this step
+        auto ahead3 = [&](int t) -> double {
+            const int u = t + 3;
             double x = u < C ? c[u < C ? u : C - 1] : (u == C ? q1 : (u == C + 1 ? q2 : q3));
             if constexpr (!FULL) {
                 const int w = u - nrow;   // ragged: past row n-1 come rows 0, 1, 2
@@ -98,26 +124,64 @@ struct ForcedChRhs {
             return x;
         };
         const bool plus = st.beta > 0.0;
+        const double bsign = plus ? -st.beta : st.beta;
+        // rows t + 1, t + 2; first differences D_i = C_{i+1} - C_i around row t
+        // (dk: D_{t+k}), their squares, pairs' maxima and second differences
+        // G_i = D_i - D_{i-1}
+        double p1, p2;
+        {
+            auto first = [&](int u) -> double {
+                double x = u < C ? c[u < C ? u : C - 1] : (u == C ? q1 : q2);
+                if constexpr (!FULL) {
+                    const int w = u - nrow;
+                    x = w < 0 ? x : (w == 0 ? h.e0 : h.e1);
+                }
+                return x;
+            };
+            p1 = first(1);
+            p2 = first(2);
+        }
+        double dm1 = c[0] - m1, d0 = p1 - c[0], d1 = p2 - p1;
+        const double dm2 = m1 - m2, dm3 = m2 - m3;
+        double gm2 = dm2 - dm3, gm1 = dm1 - dm2, g0 = d0 - dm1, g1 = d1 - d0;
+        double sm3 = dm3 * dm3, sm2 = dm2 * dm2, sm1 = dm1 * dm1, s0 = d0 * d0, s1 = d1 * d1;
+        double xm2 = fmax(sm2, sm1), xm1 = fmax(sm1, s0), x0 = fmax(s0, s1);
         double nprev = nl3(m1), ncur = nl3(c[0]);
         double cs = st.c0, sn = st.s0;
         rows_up<C>([&](int t) {
             const double cur = c[t];
-            const double p1 = ahead(t, 1), p2 = ahead(t, 2), p3 = ahead(t, 3);
+            const double p3 = ahead3(t);
             const double nnext = nl3(p1);
             double f = fma(alpha, fma(-2.0, ncur, nprev) + nnext, cur);
-            // one-sided differences from the far upwind end
-            const double v1 = plus ? p3 - p2 : m2 - m3;
-            const double v2 = plus ? p2 - p1 : m1 - m2;
-            const double v3 = plus ? p1 - cur : cur - m1;
-            const double v4 = plus ? cur - m1 : p1 - cur;
-            const double v5 = plus ? m1 - m2 : p2 - p1;
-            f = fma(st.beta, weno5(v1, v2, v3, v4, v5), f);
+            const double d2 = p3 - p2, g2 = d2 - d1, s2 = d2 * d2;
+            // upwind: rows below (beta > 0) or above; the second differences of
+            // the rows below enter negated, which the sign of bsign carries
+            const double a = plus ? g2 : gm2, b = plus ? g1 : gm1, d = plus ? gm1 : g1;
+            const double v3 = plus ? d0 : dm1;
+            const double vmax2 = fmax(fmax(xm2, x0), plus ? s2 : sm3);
+            const double rest = weno5_rest(a, b, g0, d, vmax2);
+            f = fma(st.beta, v3, f);
+            f = fma(bsign, rest, f);
             f = fma(st.amp, cs, f);
             if constexpr (!FULL) f = t < nrow ? f : 0.0;
             c[t] = f;
-            m3 = m2;
-            m2 = m1;
-            m1 = cur;
+            p1 = p2;
+            p2 = p3;
+            dm1 = d0;
+            d0 = d1;
+            d1 = d2;
+            gm2 = gm1;
+            gm1 = g0;
+            g0 = g1;
+            g1 = g2;
+            sm3 = sm2;
+            sm2 = sm1;
+            sm1 = s0;
+            s0 = s1;
+            s1 = s2;
+            xm2 = xm1;
+            xm1 = x0;
+            x0 = fmax(s0, s1);
             nprev = ncur;
             ncur = nnext;
             const double cn = fma(cs, st.cd, -sn * st.sd);   // rotate to row t + 1
