@@ -48,6 +48,13 @@ def _side_stream(device, which: int) -> "torch.cuda.Stream":
     return _SIDE_STREAMS[key]
 
 
+def _band_grads(gb, devices):
+    """The rows of gb on the bands' devices, one copy per device: a copy to the
+    host waits for the device each time."""
+    on = {d: gb.to(d) for d in set(devices)}
+    return [on[d][q] for q, d in enumerate(devices)]
+
+
 def _kind(nb: int) -> str:
     if nb not in (3, 5):
         raise ValueError("need 3 (tri) or 5 (penta) bands")
@@ -72,7 +79,7 @@ class BandedSolve(torch.autograd.Function):
         f = ctx.factor
         lam = f.adjoint(gx.contiguous(), precision=ctx.precision)
         gb = f.band_grad(lam, x)
-        return (lam, None, None, *[gb[q].to(d) for q, d in enumerate(ctx.band_devices)])
+        return (lam, None, None, *_band_grads(gb, ctx.band_devices))
 
 
 def banded_solve(rhs, bands, cyclic: bool = False, precision: str = "f64"):
@@ -200,8 +207,7 @@ class BandedRollout(torch.autograd.Function):
             del states
         main.wait_stream(side)
         ctx.checkpoints = None
-        return (g, None, None, None, None,
-                *[gb[q].to(d) for q, d in enumerate(ctx.band_devices)])
+        return (g, None, None, None, None, *_band_grads(gb, ctx.band_devices))
 
 
 def banded_rollout(u0, bands, steps: int, checkpoint_every: int = 10, precision: str = "f64",

@@ -769,6 +769,42 @@ int cu_count()
     return cached;
 }
 
+// Workgroups of a kernel that fit a CU at once, asked of the runtime once per
+// thread, device, kernel and launch shape (the questions took about 1 us of a
+// 4 us call); a kernel that needs more than 64 KB of LDS is allowed it then.
+struct ResidentKey {
+    const void *kern = nullptr;
+    size_t lds = 0;
+    int threads = 0, dev = 0, blocks = 0;
+};
+
+inline hipError_t resident_blocks(const void *kern, int threads, size_t lds, int *blocks)
+{
+    constexpr int N = 64;   // direct-mapped, so bounded
+    static thread_local ResidentKey cache[N];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    ResidentKey &c = cache[(((uintptr_t)kern >> 4) ^ (lds >> 3) ^ (uintptr_t)dev) % N];
+    if (c.kern == kern && c.lds == lds && c.threads == threads && c.dev == dev) {
+        *blocks = c.blocks;
+        return hipSuccess;
+    }
+    if (lds > 65536) {
+        // the CU's whole LDS: launches of one kernel differ in what they need
+        e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, kern, threads, lds);
+    if (e != hipSuccess) return e;
+    c.kern = kern;
+    c.lds = lds;
+    c.threads = threads;
+    c.dev = dev;
+    c.blocks = *blocks;
+    return hipSuccess;
+}
+
 // Persistent-style launch: as many workgroups as can be resident at once
 // (rounded to a multiple of the 8 XCDs), each looping over groups of systems.
 // split_waves > 0: a split group of that many waves is the whole workgroup.
@@ -783,11 +819,6 @@ template <typename... KArgs, typename... Args>
 hipError_t launch_grid_mode(void (*kern)(KArgs...), size_t lds, int64_t groups, int split_waves,
                             bool linear, hipStream_t s, Args... args)
 {
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
     // waves per workgroup: the workgroup is the unit that moves in step (see
     // begin_block); tuning waves_per_block (1, 2 or 4) overrides
     int waves_per_block = kBlockThreads / kWave;
@@ -799,7 +830,7 @@ hipError_t launch_grid_mode(void (*kern)(KArgs...), size_t lds, int64_t groups, 
     }
     const int threads = waves_per_block * kWave;
     int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds);
+    hipError_t e = resident_blocks((const void *)kern, threads, lds, &per_cu);
     if (e != hipSuccess) return e;
     if (per_cu < 1) return hipErrorInvalidConfiguration;
     int64_t need = (groups + groups_per_block - 1) / groups_per_block;

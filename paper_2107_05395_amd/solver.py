@@ -19,11 +19,42 @@ from ._lib import BandBatchError, check, dptr, lib
 KINDS = ("tri", "tri_cyclic", "penta", "penta_cyclic")
 
 
-def _stream_ptr(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+# A solve of a small batch takes about 6 us on the device and in the C call;
+# the marshalling around it is kept near 2 us (it was 7): the current stream's
+# handle straight from the runtime binding that torch's own launchers use,
+# addresses passed as plain integers, no device switch when the tensor's
+# device is current, and one look at a contiguous batch.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_ptr(t: torch.Tensor) -> int:
+    if _raw_stream is not None:
+        return _raw_stream(t.device.index)
+    return torch.cuda.current_stream(t.device).cuda_stream
+
+
+class _NoSwitch:
+    def __enter__(self):
+        return None
+
+    def __exit__(self, *exc):
+        return False
+
+
+_NO_SWITCH = _NoSwitch()
+
+
+def _on(device: torch.device):
+    """Context with `device` current."""
+    return _NO_SWITCH if device.index == torch.cuda.current_device() else torch.cuda.device(device)
 
 
 def _batch_view(t: torch.Tensor, n: int, dtype: torch.dtype, what: str):
+    if t.dtype is dtype and t.is_cuda and t.is_contiguous():
+        shape = t.shape
+        if len(shape) == 2 and shape[0] == n:
+            m = shape[1]
+            return m, m or 1
     if not t.is_cuda:
         raise ValueError("%s must be a device tensor" % what)
     if t.dtype != dtype:
@@ -111,21 +142,24 @@ class Factor:
             check(lib().bb_factor_upload(self._handle, None))
 
     # ------------------------------------------------------------ solves
-    def _run(self, fname: str, rhs: torch.Tensor, out, precision: str):
-        if precision not in _lib.PRECISION:
+    def _run(self, adjoint: bool, rhs: torch.Tensor, out, precision: str):
+        code = _lib.PRECISION.get(precision)
+        if code is None:
             raise ValueError("precision must be one of %s" % list(_lib.PRECISION))
         in_dtype = torch.float32 if precision in ("f32", "f32rhs", "f32rhs_f64") else torch.float64
         out_dtype = torch.float32 if precision == "f32" else torch.float64
         m, ld = _batch_view(rhs, self.n, in_dtype, "rhs")
         if out is None:
             out = torch.empty_like(rhs, dtype=out_dtype)
-        m2, ld2 = _batch_view(out, self.n, out_dtype, "out")
-        if (m2, ld2) != (m, ld) or out.device != rhs.device:
+        if _batch_view(out, self.n, out_dtype, "out") != (m, ld) or out.device != rhs.device:
             raise ValueError("out must match rhs in shape, strides and device")
-        with torch.cuda.device(rhs.device):
-            check(getattr(lib(), fname)(self._handle, ctypes.c_void_p(rhs.data_ptr()),
-                                        ctypes.c_void_p(out.data_ptr()), m, ld,
-                                        _lib.PRECISION[precision], _stream_ptr(rhs)))
+        L = lib()
+        if self.nbands == 3:
+            fn = L.bb_solve_batch_tri_adjoint if adjoint else L.bb_solve_batch_tri
+        else:
+            fn = L.bb_solve_batch_penta_adjoint if adjoint else L.bb_solve_batch_penta
+        with _on(rhs.device):
+            check(fn(self._handle, rhs.data_ptr(), out.data_ptr(), m, ld, code, _stream_ptr(rhs)))
         return out
 
     def solve(self, rhs: torch.Tensor, out: torch.Tensor | None = None,
@@ -138,22 +172,21 @@ class Factor:
         "f32rhs_f64" (float rhs data promoted exactly and solved with the FP64
         sweeps, double x).  out may be rhs (in place) except with "f32rhs" and
         "f32rhs_f64"."""
-        return self._run("bb_solve_batch_" + self.kind.replace("_cyclic", ""), rhs, out, precision)
+        return self._run(False, rhs, out, precision)
 
     def adjoint(self, g: torch.Tensor, out: torch.Tensor | None = None,
                 precision: str = "f64") -> torch.Tensor:
         """lam = A^{-T} g for every column."""
-        return self._run("bb_solve_batch_" + self.kind.replace("_cyclic", "") + "_adjoint", g, out,
-                         precision)
+        return self._run(True, g, out, precision)
 
     def solve_thread_per_system(self, rhs: torch.Tensor, out: torch.Tensor | None = None):
         """The paper's one-thread-per-system sweep (baseline design; tri, double)."""
         m, ld = _batch_view(rhs, self.n, torch.float64, "rhs")
         if out is None:
             out = torch.empty_like(rhs)
-        with torch.cuda.device(rhs.device):
+        with _on(rhs.device):
             check(lib().bb_solve_batch_tri_thread_per_system(
-                self._handle, ctypes.c_void_p(rhs.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+                self._handle, rhs.data_ptr(), out.data_ptr(),
                 m, ld, _stream_ptr(rhs)))
         return out
 
@@ -177,11 +210,11 @@ class Factor:
             raise ValueError("grad must be a contiguous (nbands, n) float64 tensor")
         nbytes = lib().bb_band_grad_workspace_bytes(self._handle, m)
         ws = torch.empty(max(nbytes, 8), dtype=torch.uint8, device=lam.device)
-        with torch.cuda.device(lam.device):
-            check(lib().bb_band_grad(self._handle, ctypes.c_void_p(lam.data_ptr()),
-                                     ctypes.c_void_p(x.data_ptr()), m, ld,
-                                     ctypes.c_void_p(grad.data_ptr()),
-                                     ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream_ptr(lam)))
+        with _on(lam.device):
+            check(lib().bb_band_grad(self._handle, lam.data_ptr(),
+                                     x.data_ptr(), m, ld,
+                                     grad.data_ptr(),
+                                     ws.data_ptr(), ws.numel(), _stream_ptr(lam)))
         return grad
 
     def band_grad_noalloc(self, lam: torch.Tensor, x: torch.Tensor,
@@ -193,10 +226,10 @@ class Factor:
             raise ValueError("x must match lam in shape and strides")
         if grad.shape != (self.nbands, self.n) or grad.dtype != torch.float64 or not grad.is_contiguous():
             raise ValueError("grad must be a contiguous (nbands, n) float64 tensor")
-        with torch.cuda.device(lam.device):
-            check(lib().bb_band_grad_noalloc(self._handle, ctypes.c_void_p(lam.data_ptr()),
-                                             ctypes.c_void_p(x.data_ptr()), m, ld,
-                                             ctypes.c_void_p(grad.data_ptr()), _stream_ptr(lam)))
+        with _on(lam.device):
+            check(lib().bb_band_grad_noalloc(self._handle, lam.data_ptr(),
+                                             x.data_ptr(), m, ld,
+                                             grad.data_ptr(), _stream_ptr(lam)))
         return grad
 
     def ch_step(self, c: torch.Tensor, alpha: float, steps: int = 1,
@@ -207,9 +240,9 @@ class Factor:
             out = torch.empty_like(c)
         if _batch_view(out, self.n, torch.float64, "out") != (m, ld):
             raise ValueError("out must match c in shape and strides")
-        with torch.cuda.device(c.device):
-            check(lib().bb_ch_step(self._handle, ctypes.c_void_p(c.data_ptr()),
-                                   ctypes.c_void_p(out.data_ptr()), m, ld, float(alpha),
+        with _on(c.device):
+            check(lib().bb_ch_step(self._handle, c.data_ptr(),
+                                   out.data_ptr(), m, ld, float(alpha),
                                    int(steps), _stream_ptr(c)))
         return out
 
@@ -247,13 +280,13 @@ class Factor:
             raise ValueError("out must match c in shape and strides")
         samples = int(steps) // int(every) if every >= 1 else 0
         lbar = torch.empty(max(samples, 1), dtype=torch.float64, device=c.device)
-        with torch.cuda.device(c.device):
+        with _on(c.device):
             nbytes = lib().bb_ch_stats_workspace_bytes(self._handle, m, samples)
             ws = torch.empty(max(nbytes, 8), dtype=torch.uint8, device=c.device)
-            check(lib().bb_ch_step_stats(self._handle, ctypes.c_void_p(c.data_ptr()),
-                                         ctypes.c_void_p(out.data_ptr()), m, ld, float(alpha),
-                                         int(steps), int(every), ctypes.c_void_p(lbar.data_ptr()),
-                                         ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+            check(lib().bb_ch_step_stats(self._handle, c.data_ptr(),
+                                         out.data_ptr(), m, ld, float(alpha),
+                                         int(steps), int(every), lbar.data_ptr(),
+                                         ws.data_ptr(), ws.numel(),
                                          _stream_ptr(c)))
         return out, lbar[:samples]
 
@@ -272,12 +305,12 @@ class Factor:
             out = torch.empty_like(c)
         if _batch_view(out, self.n, torch.float64, "out") != (m, ld):
             raise ValueError("out must match c in shape and strides")
-        with torch.cuda.device(c.device):
-            check(lib().bb_ch_forced_step(self._handle, ctypes.c_void_p(c.data_ptr()),
-                                          ctypes.c_void_p(out.data_ptr()), m, ld, float(dt),
-                                          float(dx), ctypes.c_void_p(v.data_ptr()),
-                                          ctypes.c_void_p(f0.data_ptr()),
-                                          ctypes.c_void_p(k.data_ptr()), int(steps),
+        with _on(c.device):
+            check(lib().bb_ch_forced_step(self._handle, c.data_ptr(),
+                                          out.data_ptr(), m, ld, float(dt),
+                                          float(dx), v.data_ptr(),
+                                          f0.data_ptr(),
+                                          k.data_ptr(), int(steps),
                                           _stream_ptr(c)))
         return out
 
@@ -309,9 +342,9 @@ class Factor:
         if len(w) != self.nbands:
             raise ValueError("need %d stencil weights" % self.nbands)
         wv = (ctypes.c_double * len(w))(*(float(x) for x in w))
-        with torch.cuda.device(c.device):
+        with _on(c.device):
             check(lib().bb_cn_step(self._handle, ctypes.cast(wv, ctypes.c_void_p),
-                                   ctypes.c_void_p(c.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+                                   c.data_ptr(), out.data_ptr(),
                                    m, ld, int(steps), _stream_ptr(c)))
         return out
 
@@ -326,10 +359,10 @@ class Factor:
             raise ValueError("steps must be >= 1")
         traj = torch.empty((steps, self.n, ld), dtype=torch.float64, device=c.device)[:, :, :m]
         wv = (ctypes.c_double * len(w))(*(float(x) for x in w))
-        with torch.cuda.device(c.device):
+        with _on(c.device):
             check(lib().bb_cn_trajectory(self._handle, ctypes.cast(wv, ctypes.c_void_p),
-                                         ctypes.c_void_p(c.data_ptr()),
-                                         ctypes.c_void_p(traj.data_ptr()), m, ld, int(steps),
+                                         c.data_ptr(),
+                                         traj.data_ptr(), m, ld, int(steps),
                                          _stream_ptr(c)))
         return traj
 
@@ -342,9 +375,9 @@ class Factor:
         if steps < 1:
             raise ValueError("steps must be >= 1")
         traj = torch.empty((steps, self.n, ld), dtype=torch.float64, device=g.device)[:, :, :m]
-        with torch.cuda.device(g.device):
-            check(lib().bb_adjoint_trajectory(self._handle, ctypes.c_void_p(g.data_ptr()),
-                                              ctypes.c_void_p(traj.data_ptr()), m, ld, int(steps),
+        with _on(g.device):
+            check(lib().bb_adjoint_trajectory(self._handle, g.data_ptr(),
+                                              traj.data_ptr(), m, ld, int(steps),
                                               _stream_ptr(g)))
         return traj
 
@@ -370,12 +403,12 @@ class Factor:
         lam = torch.empty((self.n, ld), dtype=torch.float64, device=g.device)[:, :m]
         nbytes = lib().bb_adjoint_band_grad_workspace_bytes(self._handle, m, ld)
         ws = torch.empty(max(nbytes, 8), dtype=torch.uint8, device=g.device)
-        with torch.cuda.device(g.device):
-            check(lib().bb_adjoint_band_grad(self._handle, ctypes.c_void_p(g.data_ptr()),
-                                             ctypes.c_void_p(traj.data_ptr()),
-                                             ctypes.c_void_p(lam.data_ptr()), m, ld, int(steps),
-                                             ctypes.c_void_p(grad.data_ptr()),
-                                             ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+        with _on(g.device):
+            check(lib().bb_adjoint_band_grad(self._handle, g.data_ptr(),
+                                             traj.data_ptr(),
+                                             lam.data_ptr(), m, ld, int(steps),
+                                             grad.data_ptr(),
+                                             ws.data_ptr(), ws.numel(),
                                              _stream_ptr(g)))
         return lam, grad
 
@@ -412,12 +445,12 @@ def mse_loss_grad(u: torch.Tensor, target: torch.Tensor, grad: torch.Tensor | No
     loss = torch.empty((), dtype=torch.float64, device=u.device)
     nbytes = lib().bb_mse_workspace_bytes(n, m)
     ws = torch.empty(max(nbytes, 8), dtype=torch.uint8, device=u.device)
-    with torch.cuda.device(u.device):
-        check(lib().bb_mse_loss_grad(ctypes.c_void_p(u.data_ptr()),
-                                     ctypes.c_void_p(target.data_ptr()),
-                                     ctypes.c_void_p(grad.data_ptr()),
-                                     ctypes.c_void_p(loss.data_ptr()), n, m, ld,
-                                     ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream_ptr(u)))
+    with _on(u.device):
+        check(lib().bb_mse_loss_grad(u.data_ptr(),
+                                     target.data_ptr(),
+                                     grad.data_ptr(),
+                                     loss.data_ptr(), n, m, ld,
+                                     ws.data_ptr(), ws.numel(), _stream_ptr(u)))
     return loss, grad
 
 
@@ -429,8 +462,8 @@ def copy_tiles(src: torch.Tensor, dst: torch.Tensor) -> torch.Tensor:
     nbytes = src.numel() * src.element_size()
     if dst.numel() * dst.element_size() != nbytes:
         raise ValueError("src and dst differ in size")
-    with torch.cuda.device(src.device):
-        check(lib().bb_copy_tiles(ctypes.c_void_p(src.data_ptr()), ctypes.c_void_p(dst.data_ptr()),
+    with _on(src.device):
+        check(lib().bb_copy_tiles(src.data_ptr(), dst.data_ptr(),
                                   nbytes, _stream_ptr(src)))
     return dst
 
@@ -443,8 +476,8 @@ def copy_rows(src: torch.Tensor, dst: torch.Tensor) -> torch.Tensor:
     m, ld = _batch_view(src, n, torch.float64, "src")
     if _batch_view(dst, n, torch.float64, "dst") != (m, ld):
         raise ValueError("dst must match src in shape and strides")
-    with torch.cuda.device(src.device):
-        check(lib().bb_copy_rows(ctypes.c_void_p(src.data_ptr()), ctypes.c_void_p(dst.data_ptr()),
+    with _on(src.device):
+        check(lib().bb_copy_rows(src.data_ptr(), dst.data_ptr(),
                                  n, m, ld, _stream_ptr(src)))
     return dst
 
