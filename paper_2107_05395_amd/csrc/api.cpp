@@ -185,11 +185,13 @@ int split_log2(int log2P, int C, int n, bb::Op op, bool f32_in = false)
 struct StepPlan {
     int C, P, log2P, log2Q;
     bool scalar;   // one chunk per wave, coefficients through the scalar cache
+    int waves = 0; // > 0: that, on as many waves as n has chunks (P), any number up to 8
 };
 
 // Rows per lane: 64 (two waves per SIMD), or latency_chunk for small
 // batches, or 32 below two waves per SIMD where that keeps one chunk per wave.  Systems split over several waves when the chunks tile n: one
-// chunk per wave with scalar coefficients up to 8 chunks, else the LDS table
+// chunk per wave with scalar coefficients up to 8 chunks (also where they do
+// not tile n), else the LDS table
 // with 32 systems per group (4 waves at P = 8, 8 waves from P = 16; n = 1024,
 // m = 2^16: 0.063 vs 0.096 ms per tri step over one wave per group).
 // A tridiagonal group of 16 chunks that keeps its state on chip runs as 16
@@ -210,10 +212,16 @@ StepPlan step_plan(int K, int64_t n, int64_t m, bool states = false)
         // 200 fused steps, 64 vs 32 rows: penta n = 64, m = 2^16 0.84 vs
         // 0.71; n = 128, m = 2^15 1.18 vs 0.80; n = 256, m = 2^14 1.22 vs
         // 0.98; CH n = 64, m = 2^16 0.87 vs 0.67; equal or worse from 2^17
-        // lanes on.
-        if (C == 64 && lanes64 < (int64_t(1) << 17) && 32LL * bb::lanes_for(n, 32) == n &&
-            bb::lanes_for(n, 32) <= 8)
-            C = 32;
+        // lanes on.  So too where chunks do not tile n (us per step: penta
+        // n = 200, m = 2^14 9.5 vs 6.3, m = 2^15 11.0 vs 12.2).
+        if (C == 64 && lanes64 < (int64_t(1) << 17) && n > 32 && (n + 31) / 32 <= 8) C = 32;
+        // Too many 32-row chunks for a wave each: one wave per group of
+        // systems holds them while a SIMD has one wave, then 64-row chunks
+        // with a wave each are faster (us per step at m = 2000 and 5000:
+        // penta n = 500 7.7 vs 9.3, 11.2 vs 9.4; tri 5.7 vs 6.3, 7.1 vs 6.4)
+        if (C == 32 && n > 256 && (n + 63) / 64 <= 8 && 64LL * bb::lanes_for(n, 64) != n &&
+            m * bb::lanes_for(n, 32) > (int64_t(1) << 16))
+            C = 64;
     }
     StepPlan pl;
     pl.C = C;
@@ -227,6 +235,19 @@ StepPlan step_plan(int K, int64_t n, int64_t m, bool states = false)
         pl.log2Q = pl.log2P;
     else if (full && C >= 32 && pl.log2P >= 3)
         pl.log2Q = pl.log2P >= 4 && !(K == 1 && C == 64 && pl.log2P == 4 && !states) ? 3 : 2;
+    // n that no power-of-two number of chunks tiles: one chunk per wave too, on
+    // as many waves as n has chunks.  Against one wave per group with LDS
+    // coefficients, whose every wave takes the row predicates and which works
+    // on padding up to a power of two (us per step): penta n = 500, m = 2^16
+    // 38.7 vs 73.7; n = 384, m = 2^16 31.6 vs 66.3; n = 200, m = 2^13 6.1 vs
+    // 7.9; tri n = 300, m = 50000 19.8 vs 31.5; n = 40, m = 2^16 4.7 vs 7.5
+    const int64_t real = (n + C - 1) / C;
+    if (!pl.scalar && (C == 32 || C == 64) && real <= 8 &&
+        bb::tuning(bb::kTuneChUniform) != 0 && bb::tuning(bb::kTuneWavesPerSystem) < 0) {
+        pl.P = pl.waves = (int)real;
+        pl.scalar = true;
+        return pl;
+    }
     if (bb::tuning(bb::kTuneWavesPerSystem) > 0 && !pl.scalar && full && C >= 32) {
         const int64_t q = bb::tuning(bb::kTuneWavesPerSystem);
         const int fl = q == 1 ? 0 : q == 2 ? 1 : q == 4 ? 2 : 3;
@@ -245,10 +266,15 @@ bb::SweepGeom step_geom(int64_t n, int64_t m, int64_t ld, const StepPlan &pl)
     g.m = m;
     g.ld = ld;
     g.log2Q = pl.log2Q;
-    const int S = (bb::kWave << g.log2Q) / pl.P;
+    const int S = pl.waves > 0 ? bb::kWave : (bb::kWave << g.log2Q) / pl.P;   // systems per group
     g.groups = (m + S - 1) / S;
     g.lockstep = lockstep_for(g.log2Q > 0);
     g.linear = grid_linear() < 0 ? pl.scalar : grid_linear();
+    g.waves = pl.waves;
+    if (pl.waves > 0) {   // the kernel's grid is one workgroup per group
+        g.lockstep = 0;
+        g.linear = 1;
+    }
     return g;
 }
 
@@ -382,7 +408,8 @@ bb_status stepper_setup(bb::Factor &f, int dev, int64_t m, int64_t ld, StepPlan 
     const int C = pl->C, P = pl->P;
     // the same table as a solve (or adjoint solve) with this chunk size
     const bb::Direction &dir = adjoint ? f.adjoint : f.primal;
-    bb_status st = device_table(f, f.dev, std::make_tuple(dev, (int)adjoint, 0, C, 0), false,
+    // (key slot 4 = 3: as many chunks as n has, not a power of two)
+    bb_status st = device_table(f, f.dev, std::make_tuple(dev, (int)adjoint, 0, C, pl->waves > 0 ? 3 : 0), false,
                                 [&] { return bb::build_sweep_table(dir, f.K, f.cyclic, f.n, C, P); },
                                 tab);
     if (st != BB_OK) return st;
@@ -615,7 +642,7 @@ bb_status bb_plan(bb_factor fh, int64_t m, int32_t what, bb_precision p, int32_t
         p != BB_F32_RHS_F64)
         return fail(BB_ERR_ARG, "unknown precision");
     const bb::Factor &f = fh->f;
-    int C, P, log2Q, sc = 0;
+    int C, P, log2Q, sc = 0, rag_waves = 0;
     if (is_long(f)) {
         // three launches, one chunk of 64 systems per wave, coefficients
         // through the scalar cache
@@ -636,11 +663,12 @@ bb_status bb_plan(bb_factor fh, int64_t m, int32_t what, bb_precision p, int32_t
         C = pl.C;
         P = pl.P;
         log2Q = pl.log2Q;
+        rag_waves = pl.waves;
         sc = pl.scalar ? 1 : 0;
     }
     if (chunk) *chunk = C;
     if (lanes) *lanes = P;
-    if (waves) *waves = 1 << log2Q;
+    if (waves) *waves = rag_waves > 0 ? rag_waves : 1 << log2Q;
     if (scalar) *scalar = sc;
     g_last_error.clear();
     return BB_OK;
@@ -823,7 +851,7 @@ bb_status ch_steps(bb_factor fh, const double *c_in, double *c_out, int64_t m, i
     if ((st = stepper_setup(f, dev, m, ld, &pl, &tab, &g)) != BB_OK) return st;
     // with the statistic the persistent grid measured faster (coarsening
     // n = 256, m = 2^20, 2000 steps per launch: 0.209 vs 0.226 ms per step)
-    if (samples > 0 && grid_linear() < 0) g.linear = 0;
+    if (samples > 0 && grid_linear() < 0 && g.waves == 0) g.linear = 0;
     hipError_t e = bb::launch_ch((const double *)tab.ptr, tab.elems, f.primal.cor.q, g, pl.scalar,
                                  alpha, steps, c_in, c_out, (hipStream_t)stream, every, samples,
                                  (double *)workspace, lbar);

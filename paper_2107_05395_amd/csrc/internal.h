@@ -125,6 +125,7 @@ struct SweepGeom {
     int lockstep;   // workgroup barrier at the start of every persistent-loop iteration
     int log2Q;      // waves per system group (0: a group is one wave)
     int linear = 0; // one workgroup per block of groups, in launch order (no persistent loop)
+    int waves = 0;  // > 0: fused stepper with one chunk per wave on that many waves, any number
 };
 
 // Split groups of up to 4 waves, or 8 when the kernel runs two waves per SIMD

@@ -149,6 +149,30 @@ __global__ __launch_bounds__(kMaxBlockThreads) void step_kernel(const double *__
     }
 }
 
+// Any number of waves per group: chunks that tile n, or a last chunk with padding.
+constexpr int kRagFull = 1, kRagTail = 2;
+
+// x = v[t], or v[t] = x (PUT), for a wave-uniform t: a tree of scalar branches.
+// The fence that ends each leaf keeps the compiler from merging them into one
+// indexed access, for which it would put the whole chunk into scratch memory.
+template <bool PUT, int LO, int HI, int C>
+__device__ __forceinline__ void row_at(double (&v)[C], int t, double &x)
+{
+    if constexpr (HI - LO == 1) {
+        if constexpr (PUT)
+            v[LO] = x;
+        else
+            x = v[LO];
+        asm volatile("" : "+v"(x));
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (t < MID)
+            row_at<PUT, LO, MID>(v, t, x);
+        else
+            row_at<PUT, MID, HI>(v, t, x);
+    }
+}
+
 // Waves per SIMD a split kernel is held to.  Three, with 64-row chunks in 168
 // VGPRs, where the compiler gets there without spills (a workgroup of four
 // waves or fewer, at most two halo rows): a step waits at its barriers and
@@ -172,16 +196,24 @@ constexpr int step_waves(int K, int C, int QL, bool scalar, int rows, int R)
 // the table is staged in LDS ahead of the exchange area.
 // ROWS: chunks per wave (2 or 4) of a group whose LDS coefficients go by row
 // broadcast, 0: plain LDS reads.
+// RAG (scalar): any number of waves up to 2^QL, each with one chunk of C rows;
+// kRagFull: they tile n, kRagTail: the last holds the rows that remain.  Only
+// that wave loads and stores with row predicates, and periodic ghost rows in
+// its padding let it run the right-hand side of a full chunk (a second,
+// predicated copy of the right-hand side put 0.5-1.5 KB of every lane into
+// scratch).  Times beside the rule (step_plan).
 template <class Rhs, int K, bool CYC, int C, int QL, bool SCALAR, bool STATS, bool TRAJ,
-          int ROWS = 0>
+          int ROWS = 0, int RAG = 0>
 __global__ __launch_bounds__((kWave << QL) > kMaxBlockThreads ? (kWave << QL) : kMaxBlockThreads,
                              step_waves(K, C, QL, SCALAR, ROWS, Rhs::R))
 void step_kernel_split(const double *__restrict__ table, int64_t table_elems, CyclicQ cq,
                        SweepGeom g, Rhs rhs, int64_t steps, StepStats st, const double *in,
                        double *out)
 {
+    static_assert(RAG == 0 || SCALAR, "any number of waves: one chunk each");
     using Src = typename std::conditional<SCALAR, FromScalar<double>, FromLds<double>>::type;
     constexpr int R = Rhs::R;
+    constexpr bool FULL = RAG != kRagTail;
     extern __shared__ double smem_d[];
     const int64_t tl = SCALAR ? 0 : table_elems;
     double *xch = smem_d + tl;                              // chunk_solve phases
@@ -199,8 +231,20 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
     // SCALAR: P == Q (the host checks log2P == QL), so the geometry is known
     // at compile time: S = 64, one chunk per wave
     LaneGeom lg = lane_geom(SCALAR ? QL : ROWS > 0 ? QL + ROWS / 2 : g.log2P, QL);
+    if constexpr (RAG != 0) {
+        lg.P = g.waves;
+        lg.S = kWave;
+        lg.W = 1;
+        lg.sl = threadIdx.x % kWave;
+        lg.j0 = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    }
     if constexpr (SCALAR) lg.j = lg.j0;   // the wave's chunk
     const int row0 = lg.j * C;
+    // kRagTail: rows of the system from this chunk on; whether the wave's rows
+    // are all real, and its stencil's too
+    const int nrow = g.n - row0;
+    const bool all_real = FULL || nrow >= C;
+    double *xe = xs + (STATS ? (kWave << QL) : 0);          // kRagTail: rows n-1 .. n-R
     const bool has_left = lg.j > 0, has_right = lg.j < lg.P - 1;
     const int PS = lg.P * lg.S;
     const int me = lg.j * lg.S + lg.sl;
@@ -210,7 +254,11 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
     // STATS launches are persistent unless forced (the mapping code costs the
     // statistic kernel its third wave per SIMD); the persistent mapping also
     // serves a forced one-per-group grid
-    const GroupRange gr = group_range(g.groups, QL, STATS ? 0 : g.linear);
+    GroupRange gr;
+    if constexpr (RAG != 0)   // one group per workgroup, whatever its waves; no more than that
+        gr = GroupRange{blockIdx.x, blockIdx.x < g.groups ? blockIdx.x + int64_t(1) : 0, 1, 1, 0};
+    else
+        gr = group_range(g.groups, QL, STATS ? 0 : g.linear);
 
     for (int64_t blk = gr.first; blk < gr.end; blk += gr.stride) {
         const int64_t grp = begin_block(gr, blk, g.lockstep);
@@ -218,7 +266,10 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
         const int64_t k = grp * lg.S + lg.sl;
         const bool kval = k < g.m;
         double c[C];
-        load_chunk<double, C, true>(c, in, row0, kval ? k : g.m - 1, g.ld, g.n);
+        if (all_real)
+            load_chunk<double, C, true>(c, in, row0, kval ? k : g.m - 1, g.ld, g.n);
+        else
+            load_chunk<double, C, false>(c, in, row0, kval ? k : g.m - 1, g.ld, g.n);
         const typename Rhs::State ls = rhs.lane_state(kval ? k : g.m - 1, row0);
 
         for (int64_t step = 0; step < steps; ++step) {
@@ -231,6 +282,15 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
             if constexpr (R >= 3) {
                 xd[4 * PS + me] = c[2];
                 xd[5 * PS + me] = c[C - 3];
+            }
+            if constexpr (!FULL) {
+#pragma unroll
+                for (int d = 1; d <= R; ++d)
+                    if (nrow >= d && nrow - d < C) {
+                        double x = 0.0;
+                        row_at<false, 0, C>(c, opaque_u(nrow - d), x);
+                        xe[(d - 1) * kWave + lg.sl] = x;
+                    }
             }
             __syncthreads();
             Halo h = {};
@@ -250,9 +310,28 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
                 h.e2 = xd[4 * PS + first];
                 h.en3 = xd[5 * PS + last];
             }
-            rhs.template operator()<C, true>(c, h, lg.j, !has_right, C, ls);
+            if constexpr (!FULL) {
+                h.en1 = xe[lg.sl];
+                if constexpr (R >= 2) h.en2 = xe[kWave + lg.sl];
+                if constexpr (R >= 3) h.en3 = xe[2 * kWave + lg.sl];
+            }
+            if constexpr (!FULL && CYC) {
+                // rows 0 .. R-1 after row n-1, in the chunk's padding or its
+                // halo: the stencil needs no wrap terms there, and what it
+                // leaves in the padding meets zero coefficients
+                double e[3] = {h.e0, h.e1, h.e2};
+#pragma unroll
+                for (int d = 0; d < R; ++d) {
+                    const int t = opaque_u(nrow + d);
+                    if (t < C) row_at<true, 0, C>(c, t, e[d]);
+                    h.r1 = t == C ? e[d] : h.r1;
+                    h.r2 = t == C + 1 ? e[d] : h.r2;
+                    h.r3 = t == C + 2 ? e[d] : h.r3;
+                }
+            }
+            rhs.template operator()<C, true>(c, h, lg.j, FULL && !has_right, C, ls);
             __builtin_amdgcn_sched_barrier(0);
-            chunk_solve<double, K, C, CYC, true, true, Src, (ROWS > 0), (SCALAR && QL < 2 ? 1 << QL : ROWS > 0 && K == 1 ? 8 : 4)>(
+            chunk_solve<double, K, C, CYC, FULL, true, Src, (ROWS > 0), (SCALAR && QL < 2 && RAG == 0 ? 1 << QL : ROWS > 0 && K == 1 ? 8 : 4)>(
                 c, tab, lg, g.n, cq, xch);
             if (STATS && (step + 1) % st.every == 0) {
                 // chunks of a system through LDS, summed in chunk order, by
@@ -270,11 +349,17 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
                 }
             }
             if constexpr (TRAJ) {
-                if (kval) store_chunk<double, C, true>(c, out + step * st.traj_stride, row0, k, g.ld, g.n);
+                if (kval && all_real)
+                    store_chunk<double, C, true>(c, out + step * st.traj_stride, row0, k, g.ld, g.n);
+                else if (kval)
+                    store_chunk<double, C, false>(c, out + step * st.traj_stride, row0, k, g.ld, g.n);
             }
         }
         if constexpr (!TRAJ) {
-            if (kval) store_chunk<double, C, true>(c, out, row0, k, g.ld, g.n);
+            if (kval && all_real)
+                store_chunk<double, C, true>(c, out, row0, k, g.ld, g.n);
+            else if (kval)
+                store_chunk<double, C, false>(c, out, row0, k, g.ld, g.n);
         }
     }
 }
@@ -303,6 +388,28 @@ hipError_t launch_stepper(const double *table, int64_t table_elems, const Cyclic
                           const double *in, double *out, hipStream_t s,
                           StepStats st = StepStats{})
 {
+    if (g.waves > 0) {
+        // one chunk per wave on any number of waves: 32- or 64-row chunks.  A
+        // chunk with padding takes 130 to 230 VGPRs at 64 rows: QL = 3, two
+        // waves per SIMD (three, with spills: penta n = 200, m = 2^16 20.7 us a
+        // step against 16.4; tri n = 100, m = 2^17 11.1 against 9.9; the other
+        // way round at tri n = 130, 13.9 against 16.3)
+        if (g.waves > 8 || (int64_t)g.waves * g.C < g.n || (int64_t)(g.waves - 1) * g.C >= g.n)
+            return hipErrorInvalidValue;
+        const bool tail = (int64_t)g.waves * g.C != g.n;
+        const int ql = !tail && g.C == 64 && g.waves <= 4 ? 2 : 3;
+        const size_t xl = split_step_lds(K, ql, Rhs::R, STATS) + (size_t)Rhs::R * kWave * sizeof(double);
+#define BB_RAG(CC, QQ, RR)                                                                         \
+    return launch_grid_mode(step_kernel_split<Rhs, K, CYC, CC, QQ, true, STATS, TRAJ, 0, RR>, xl,  \
+                            g.groups, g.waves, true, s, table, table_elems, q, g, rhs, steps, st, in, out)
+        if (g.C == 64 && tail) BB_RAG(64, 3, kRagTail);
+        if (g.C == 64 && ql == 2) BB_RAG(64, 2, kRagFull);
+        if (g.C == 64) BB_RAG(64, 3, kRagFull);
+        if (g.C == 32 && tail) BB_RAG(32, 3, kRagTail);
+        if (g.C == 32) BB_RAG(32, 3, kRagFull);
+#undef BB_RAG
+        return hipErrorInvalidValue;
+    }
     if (scalar) {
         // one chunk per wave: 16-, 32- or 64-row chunks tiling n into at most 8
         if ((g.C != 16 && g.C != 32 && g.C != 64) || g.log2Q != g.log2P || g.log2Q > 3 || !is_full(g))
