@@ -124,10 +124,10 @@ bb_status bb_factor_info(bb_factor f, int64_t *n, int32_t *kind, int32_t *chunk)
 int64_t bb_max_n(void);
 
 /* The decomposition a call with m systems takes, without running it: rows per
- * lane (chunk), lanes per system (lanes, a power of two, chunk * lanes >= n),
- * waves per system group (waves: 1, 2, 4 or 8), and for the fused steppers
- * whether the coefficients are read through the scalar cache (scalar; one
- * chunk per wave).  what = 0: a solve or adjoint of precision p; what = 1:
+ * lane (chunk), lanes per system (lanes, chunk * lanes >= n), waves per system
+ * group (waves), and for the fused steppers whether every wave works on one
+ * chunk (scalar; then lanes == waves, any number up to 8, otherwise lanes is a
+ * power of two and waves 1, 2, 4 or 8).  what = 0: a solve or adjoint of precision p; what = 1:
  * the fused steppers (bb_ch_step, bb_ch_step_stats, bb_ch_forced_step,
  * bb_cn_step, bb_cn_trajectory; p is ignored).  Host only: no device is touched.  The tuning
  * variables of the library are honoured.  Any out pointer may be NULL.

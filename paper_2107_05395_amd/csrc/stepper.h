@@ -179,10 +179,27 @@ __device__ __forceinline__ void row_at(double (&v)[C], int t, double &x)
 // for its recurrences, and the other workgroups of the CU fill in.  The
 // Cahn-Hilliard kernel with the statistic, 2 VGPRs over: 2746 us at two
 // (n = 256, m = 2^18, 50 steps).
-constexpr int step_waves(int K, int C, int QL, bool scalar, int rows, int R)
+constexpr int step_waves(int K, int C, int QL, bool scalar, int rows, int R, int rag)
 {
-    const bool three = C == 64 && QL <= 2 && R <= 2 && (scalar || (rows == 4 && K == 1));
+    const bool three = C == 64 && QL <= 2 && R <= 2 && rag != kRagTail &&
+                       (scalar || (rows == 4 && K == 1));
     return three ? 3 : QL == 3 ? 2 : 1;
+}
+
+// Whether a kernel with one chunk per wave takes its coefficients by row
+// broadcast from an LDS table rather than through the scalar cache: the
+// passes then need neither scalar loads nor the fenced blocks of rows that
+// wait for them (us a step, scalar vs broadcast: tri n = 512, m = 2^17 39.2 vs
+// 28.8, penta 57.9 vs 46.4; penta n = 500, m = 5000 9.4 vs 8.0; penta
+// n = 200, m = 2^16 16.0 vs 14.3; 32-row chunks tri n = 128, m = 2^14 2.0 vs
+// 1.6).  Not where the scalar kernel keeps three waves per SIMD and the other,
+// which holds the pass's coefficients in VGPRs, two (Cahn-Hilliard n = 256,
+// m = 2^18 36.8 vs 38.9), nor in groups of two or three such waves (penta
+// n = 100, m = 2^17 15.5 vs 20.1).
+constexpr bool chunk_by_rows(int K, int C, int waves, int R, bool full)
+{
+    if (C == 32) return waves >= 3;
+    return C == 64 && (waves >= 5 || (waves == 4 && (!full || K == 1 || R > 2)));
 }
 
 // The same steps with a system group split over the Q = 2^QL waves of a
@@ -194,9 +211,9 @@ constexpr int step_waves(int K, int C, int QL, bool scalar, int rows, int R)
 // coefficient row at the same time, so the coefficients come from the global
 // table through the scalar cache (no LDS staging, no LDS reads).  Otherwise
 // the table is staged in LDS ahead of the exchange area.
-// ROWS: chunks per wave (2 or 4) of a group whose LDS coefficients go by row
-// broadcast, 0: plain LDS reads.
-// RAG (scalar): any number of waves up to 2^QL, each with one chunk of C rows;
+// ROWS: chunks per wave (1, 2 or 4) of a group whose LDS coefficients go by
+// row broadcast, 0: plain LDS reads.
+// RAG (one chunk per wave): any number of waves up to 2^QL, each with one chunk of C rows;
 // kRagFull: they tile n, kRagTail: the last holds the rows that remain.  Only
 // that wave loads and stores with row predicates, and periodic ghost rows in
 // its padding let it run the right-hand side of a full chunk (a second,
@@ -205,12 +222,13 @@ constexpr int step_waves(int K, int C, int QL, bool scalar, int rows, int R)
 template <class Rhs, int K, bool CYC, int C, int QL, bool SCALAR, bool STATS, bool TRAJ,
           int ROWS = 0, int RAG = 0>
 __global__ __launch_bounds__((kWave << QL) > kMaxBlockThreads ? (kWave << QL) : kMaxBlockThreads,
-                             step_waves(K, C, QL, SCALAR, ROWS, Rhs::R))
+                             step_waves(K, C, QL, SCALAR, ROWS, Rhs::R, RAG))
 void step_kernel_split(const double *__restrict__ table, int64_t table_elems, CyclicQ cq,
                        SweepGeom g, Rhs rhs, int64_t steps, StepStats st, const double *in,
                        double *out)
 {
-    static_assert(RAG == 0 || SCALAR, "any number of waves: one chunk each");
+    constexpr bool ONE = SCALAR || ROWS == 1;   // one chunk per wave
+    static_assert(RAG == 0 || ONE, "any number of waves: one chunk each");
     using Src = typename std::conditional<SCALAR, FromScalar<double>, FromLds<double>>::type;
     constexpr int R = Rhs::R;
     constexpr bool FULL = RAG != kRagTail;
@@ -228,9 +246,9 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
         tab = smem_d;
     }
 
-    // SCALAR: P == Q (the host checks log2P == QL), so the geometry is known
+    // ONE: P == Q (the host checks log2P == QL), so the geometry is known
     // at compile time: S = 64, one chunk per wave
-    LaneGeom lg = lane_geom(SCALAR ? QL : ROWS > 0 ? QL + ROWS / 2 : g.log2P, QL);
+    LaneGeom lg = lane_geom(ONE ? QL : ROWS > 0 ? QL + ROWS / 2 : g.log2P, QL);
     if constexpr (RAG != 0) {
         lg.P = g.waves;
         lg.S = kWave;
@@ -238,7 +256,7 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
         lg.sl = threadIdx.x % kWave;
         lg.j0 = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     }
-    if constexpr (SCALAR) lg.j = lg.j0;   // the wave's chunk
+    if constexpr (ONE) lg.j = lg.j0;   // the wave's chunk
     const int row0 = lg.j * C;
     // kRagTail: rows of the system from this chunk on; whether the wave's rows
     // are all real, and its stencil's too
@@ -365,71 +383,86 @@ void step_kernel_split(const double *__restrict__ table, int64_t table_elems, Cy
 }
 
 // LDS bytes of the split kernel beyond the staged table: the chunk_solve
-// exchange, 2R rows per (chunk, slot) and, for the statistic, one sum of squares
-// per (chunk, slot).
-constexpr size_t split_step_lds(int K, int QL, int R, bool stats)
+// exchange, 2R rows per (chunk, slot), for the statistic one sum of squares
+// per (chunk, slot) and, with any number of waves, R rows per slot.
+constexpr size_t split_step_lds(int K, int QL, int R, bool stats, bool rag = false)
 {
-    return (size_t)(split_exchange_len(K, QL) + ((2LL * R * kWave) << QL) + (stats ? kWave << QL : 0)) *
+    return (size_t)(split_exchange_len(K, QL) + ((2LL * R * kWave) << QL) + (stats ? kWave << QL : 0) +
+                    (rag ? R * kWave : 0)) *
            sizeof(double);
 }
 
-// Launch `steps` fused steps.  g.log2Q > 0 selects the split kernel (full
-// decomposition, log2Q <= 3), with the coefficients through the scalar cache
-// when `scalar` (then log2Q == log2P and C is 16, 32 or 64); `scalar` with
-// g.log2Q == g.log2P == 0 runs one-chunk systems the same way.  Otherwise the
-// LDS kernel with one wave per group.  The scalar kernel's grid follows
-// g.linear (it stages no table, so one workgroup per group costs nothing);
-// the LDS kernels stage the table once per workgroup and stay persistent
-// unless tuning grid_linear asks otherwise.  TRAJ: every step's state, see
-// step_kernel.
+// Launch `steps` fused steps.  `scalar` selects the kernels with one chunk
+// per wave (on g.waves waves, or on 2^log2Q == 2^log2P), otherwise
+// g.log2Q > 0 the split kernel (full decomposition, log2Q <= 3) with the table
+// in LDS, else the LDS kernel with one wave per group.  The grid of the
+// kernels with one chunk per wave follows g.linear (one that stages a table
+// reads it from L2 and still gains: penta n = 512, m = 2^17, two steps per
+// launch 171 vs 149 us a step); the other LDS kernels stage the table once per
+// workgroup and stay persistent unless tuning grid_linear asks otherwise.
+// TRAJ: every step's state, see step_kernel.
 template <class Rhs, int K, bool CYC, bool STATS = false, bool TRAJ = false>
 hipError_t launch_stepper(const double *table, int64_t table_elems, const CyclicQ &q,
                           const SweepGeom &g, bool scalar, const Rhs &rhs, int64_t steps,
                           const double *in, double *out, hipStream_t s,
                           StepStats st = StepStats{})
 {
-    if (g.waves > 0) {
-        // one chunk per wave on any number of waves: 32- or 64-row chunks.  A
-        // chunk with padding takes 130 to 230 VGPRs at 64 rows: QL = 3, two
-        // waves per SIMD (three, with spills: penta n = 200, m = 2^16 20.7 us a
-        // step against 16.4; tri n = 100, m = 2^17 11.1 against 9.9; the other
-        // way round at tri n = 130, 13.9 against 16.3)
-        if (g.waves > 8 || (int64_t)g.waves * g.C < g.n || (int64_t)(g.waves - 1) * g.C >= g.n)
-            return hipErrorInvalidValue;
-        const bool tail = (int64_t)g.waves * g.C != g.n;
-        const int ql = !tail && g.C == 64 && g.waves <= 4 ? 2 : 3;
-        const size_t xl = split_step_lds(K, ql, Rhs::R, STATS) + (size_t)Rhs::R * kWave * sizeof(double);
-#define BB_RAG(CC, QQ, RR)                                                                         \
-    return launch_grid_mode(step_kernel_split<Rhs, K, CYC, CC, QQ, true, STATS, TRAJ, 0, RR>, xl,  \
-                            g.groups, g.waves, true, s, table, table_elems, q, g, rhs, steps, st, in, out)
-        if (g.C == 64 && tail) BB_RAG(64, 3, kRagTail);
-        if (g.C == 64 && ql == 2) BB_RAG(64, 2, kRagFull);
-        if (g.C == 64) BB_RAG(64, 3, kRagFull);
-        if (g.C == 32 && tail) BB_RAG(32, 3, kRagTail);
-        if (g.C == 32) BB_RAG(32, 3, kRagFull);
-#undef BB_RAG
-        return hipErrorInvalidValue;
-    }
     if (scalar) {
-        // one chunk per wave: 16-, 32- or 64-row chunks tiling n into at most 8
-        if ((g.C != 16 && g.C != 32 && g.C != 64) || g.log2Q != g.log2P || g.log2Q > 3 || !is_full(g))
+        // one chunk per wave: 16-, 32- or 64-row chunks tiling n into 1, 2, 4
+        // or 8, or (g.waves) 32- or 64-row chunks into any number up to 8
+        const int waves = g.waves > 0 ? g.waves : 1 << g.log2Q;
+        const int64_t rows = (int64_t)waves * g.C;
+        const bool tail = rows != g.n;
+        if (waves > 8 || rows < g.n || rows - g.C >= g.n || (g.waves == 0 && (tail || g.log2P != g.log2Q)))
             return hipErrorInvalidValue;
-        const size_t xl = split_step_lds(K, g.log2Q, Rhs::R, STATS);
-#define BB_SCALAR(CC)                                                                                    \
-        case CC:                                                                                         \
-            switch (g.log2Q) {                                                                           \
-            case 0: return launch_grid_mode(step_kernel_split<Rhs, K, CYC, CC, 0, true, STATS, TRAJ>, xl, g.groups, 1, g.linear, s, table, table_elems, q, g, rhs, steps, st, in, out); \
-            case 1: return launch_grid_mode(step_kernel_split<Rhs, K, CYC, CC, 1, true, STATS, TRAJ>, xl, g.groups, 2, g.linear, s, table, table_elems, q, g, rhs, steps, st, in, out); \
-            case 2: return launch_grid_mode(step_kernel_split<Rhs, K, CYC, CC, 2, true, STATS, TRAJ>, xl, g.groups, 4, g.linear, s, table, table_elems, q, g, rhs, steps, st, in, out); \
-            default: return launch_grid_mode(step_kernel_split<Rhs, K, CYC, CC, 3, true, STATS, TRAJ>, xl, g.groups, 8, g.linear, s, table, table_elems, q, g, rhs, steps, st, in, out); \
+        const bool by_rows = chunk_by_rows(K, g.C, waves, Rhs::R, !tail);
+        const bool linear = g.waves > 0 || g.linear;
+        // QL: log2 of the waves, for any number 3 by rows and 2 (up to 3
+        // waves) with scalar coefficients.  A scalar chunk with padding takes
+        // 130 to 230 VGPRs at 64 rows: two waves per SIMD (three, with
+        // spills: tri n = 100, m = 2^17 11.1 us a step against 9.9)
+#define BB_ONE(CC, QQ, SC, RR)                                                                          \
+        return launch_grid_mode(step_kernel_split<Rhs, K, CYC, CC, QQ, SC, STATS, TRAJ, SC ? 0 : 1, RR>,\
+                                split_step_lds(K, QQ, Rhs::R, STATS, RR != 0) +                         \
+                                    (SC ? 0 : (size_t)table_elems * sizeof(double)),                    \
+                                g.groups, waves, linear, s, table, table_elems, q, g, rhs, steps, st, in, out)
+        if (by_rows) {
+            if (g.waves > 0) {
+                if (g.C == 64 && tail) BB_ONE(64, 3, false, kRagTail);
+                if (g.C == 64) BB_ONE(64, 3, false, kRagFull);
+                if (tail) BB_ONE(32, 3, false, kRagTail);
+                BB_ONE(32, 3, false, kRagFull);
             }
+            if (g.C == 64 && g.log2Q == 3) BB_ONE(64, 3, false, 0);
+            if constexpr (chunk_by_rows(K, 64, 4, Rhs::R, true))
+                if (g.C == 64) BB_ONE(64, 2, false, 0);
+            if (g.log2Q == 3) BB_ONE(32, 3, false, 0);
+            BB_ONE(32, 2, false, 0);
+        }
+        if (g.waves > 0) {
+            if (waves > 3) return hipErrorInvalidValue;
+            if (g.C == 64 && tail) BB_ONE(64, 2, true, kRagTail);
+            if (g.C == 64) BB_ONE(64, 2, true, kRagFull);
+            if (g.C == 32 && tail) BB_ONE(32, 2, true, kRagTail);
+            return hipErrorInvalidValue;
+        }
         switch (g.C) {
-            BB_SCALAR(16)
-            BB_SCALAR(32)
-            BB_SCALAR(64)
+        case 16:
+            if (g.log2Q == 3) BB_ONE(16, 3, true, 0);
+            if (g.log2Q == 2) BB_ONE(16, 2, true, 0);
+            if (g.log2Q == 1) BB_ONE(16, 1, true, 0);
+            BB_ONE(16, 0, true, 0);
+        case 32:
+            if (g.log2Q == 1) BB_ONE(32, 1, true, 0);
+            BB_ONE(32, 0, true, 0);
+        case 64:
+            if constexpr (!chunk_by_rows(K, 64, 4, Rhs::R, true))
+                if (g.log2Q == 2) BB_ONE(64, 2, true, 0);
+            if (g.log2Q == 1) BB_ONE(64, 1, true, 0);
+            BB_ONE(64, 0, true, 0);
         default: return hipErrorInvalidValue;
         }
-#undef BB_SCALAR
+#undef BB_ONE
     }
     if (g.log2Q > 0) {
         // LDS table, group split over 2^log2Q waves: 32- and 64-row chunks
