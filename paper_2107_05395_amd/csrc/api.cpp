@@ -303,7 +303,7 @@ bb::LongGeom long_geom(const bb::Factor &f, int64_t m, int64_t ld, int C)
     g.m = m;
     g.ld = ld;
     g.groups = (m + bb::kWave - 1) / bb::kWave;
-    // the scan: one wave per system while that leaves the batch's waves on
+    // the scan: a workgroup per system while that leaves the batch's waves on
     // few enough SIMDs that they run at once (a chain over the chunks in
     // each, 64 chunks per round trip to memory), else one lane per system
     const int64_t sp = bb::tuning(bb::kTuneLongSpread);

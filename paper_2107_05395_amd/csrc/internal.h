@@ -147,7 +147,7 @@ enum TuneKey : int {
     kTuneLockstep,           // 0 / 1: workgroup barrier per persistent iteration
     kTuneChUniform,          // 0: no scalar-coefficient stepper kernel
     kTuneGridLinear,         // 0 / 1: persistent or one-workgroup-per-group grids
-    kTuneLongSpread,         // 0 / 1: long-system scan with one lane or one wave per system
+    kTuneLongSpread,         // 0 / 1: long-system scan with one lane or one workgroup per system
     kTuneCount
 };
 int64_t tuning(TuneKey key);   // api.cpp
@@ -233,13 +233,13 @@ struct LongGeom {
     int n, C, P;        // rows, rows per chunk, chunks (P >= 2; chunk P-1 is the tail)
     int64_t m, ld;      // systems, leading dimension
     int64_t groups;     // groups of 64 systems
-    bool spread;        // scan with one wave per system (small batches, m <= kSpreadMax)
+    bool spread;        // scan with one workgroup per system (small batches, m <= kSpreadMax)
     bool halves;        // reduce / solve waves on two 32-system segments (m >= kHalvesMin)
 };
 constexpr int64_t kHalvesMin = 8192;
-// One wave per system scans faster than one lane per system up to 2048 systems
-// (32-row chunks) and slower from 4096 on (64-row chunks): the same boundary
-// as the chunk size.
+// A workgroup per system (one wave each above 256 systems) scans faster than
+// one lane per system up to 2048 systems (32-row chunks) and slower from 4096
+// on (64-row chunks): the same boundary as the chunk size.
 constexpr int64_t kSpreadMax = 4095;
 constexpr int64_t kMaxNLong = int64_t(1) << 18;
 hipError_t launch_long_solve(int K, bool cyclic, const double *table, const CyclicQ &q,

@@ -12,7 +12,7 @@
 //          state o_j (dot products with the table's weights), written to rows
 //          r0 .. r0+2K-1 of the solution array x, which serves as the scratch
 //          of the launch sequence;
-//   scan   (one lane per system, or one wave per system for small
+//   scan   (one lane per system, or one workgroup per system for small
 //          batches, long_scan_spread): H_j (prefix over the full chunks,
 //          H_{j+1} = e_j + Mf_j H_j) written over e_j; the tail chunk solved
 //          in registers from its history H_{P-1}; then S_j = o_j + G_j H_j and
@@ -379,15 +379,25 @@ __global__ __launch_bounds__(256) void long_solve(const double *__restrict__ tab
 }
 
 // ---------------------------------------------------------------- small batches
-// The scan with one wave per system, for batches too small for the
-// lane-per-system scan to keep more than a few lanes busy.  The lanes load
-// the values of 64 consecutive full chunks at once (lane l: chunk j0 + l),
-// keep the loads of the next two such blocks in flight while the current one
-// is scanned, and run the chain over a block as a scan of the chunks' affine
-// maps across the wave (6 rounds instead of 64 dependent steps); lane l
-// stores the state entering its chunk.  The composition rounds differently
-// from the lane scan's step-by-step chain (to a few units in the last place
-// of the chunk-boundary states); each round trip to memory serves 64 chunks.
+// The scan with one workgroup per system, for batches too small for the
+// lane-per-system scan to keep more than a few lanes busy.  The lanes of a
+// wave load the values of 64 consecutive full chunks at once (a block; the
+// loads of the wave's next block stay in flight) and turn them into a scan of
+// the chunks' affine maps across the wave (6 rounds instead of 64 dependent
+// steps); the waves scan up to kSpreadWaves consecutive blocks side by side,
+// meet once in LDS, and each then chains the maps of whole blocks up to its
+// own.  Lane l stores the state entering its chunk.  The composition rounds
+// differently from the lane scan's step-by-step chain (to a few units in the
+// last place of the chunk-boundary states); the same operations on any number
+// of waves, so the same bits.  Bound by the latency of a block's scan (6 rounds
+// of cross-lane moves, about 1 us): periodic penta
+// n = 16384, m = 8 24.4 us a solve against 32.6 with one wave per system, tri
+// n = 262144, m = 8 92 against 181.
+constexpr int kSpreadWaves = 8;   // a tail chunk of 64 rows needs their 256 VGPRs
+// One wave per system from here on: the waves of other systems fill the SIMDs
+// (penta n = 16384, m = 64 39.7 us with one wave, 31.3 with eight; m = 512
+// 96.2 and 99.7).
+constexpr int64_t kSpreadWide = 256;
 
 // one full chunk's scratch values and matrices, in the lane that holds it
 template <int K>
@@ -487,15 +497,17 @@ __device__ __forceinline__ ChunkMap<K> shfl_up_map(const ChunkMap<K> &a, int d)
     return b;
 }
 
-// The chain over one block: lane l holds the map of the l-th chunk in the
-// chain's order (the identity past the block's last chunk).  An inclusive
-// scan of the maps across the wave (log2(64) rounds of composition with the
-// lane d below) gives every lane the composition of the maps up to its own;
-// lane l's entering state is the composition up to lane l-1 applied to y,
-// and y leaves as the composition of all 64.
-template <int K>
-__device__ __forceinline__ void chain_block(ChunkMap<K> a, int lane, double &y1, double &y2,
-                                            double &my1, double &my2)
+// The chain over the blocks of a workgroup's waves, one block per wave: lane l
+// holds the map of the l-th chunk of its wave's block in the chain's order
+// (the identity past the last chunk).  An inclusive scan of the maps across
+// the wave (log2(64) rounds of composition with the lane d below) gives every
+// lane the composition of the maps up to its own; all 64 of every wave meet in
+// `blk`.  y enters the first block; lane l's entering state (my1, my2) is the
+// composition up to lane l-1 applied to the state entering its block, and y
+// leaves as the state after the last block.
+template <int K, bool WIDE>
+__device__ __forceinline__ void chain_blocks(ChunkMap<K> a, double (*blk)[K * K + K], int wave, int waves,
+                                             int lane, double &y1, double &y2, double &my1, double &my2)
 {
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
@@ -504,31 +516,62 @@ __device__ __forceinline__ void chain_block(ChunkMap<K> a, int lane, double &y1,
     }
     ChunkMap<K> p = shfl_up_map<K>(a, 1);
     if (lane == 0) p = identity_map<K>();
-    if constexpr (K == 1) {
-        my1 = fma(p.m[0], y1, p.c[0]);
-        my2 = 0.0;
-        y1 = fma(__shfl(a.m[0], kWave - 1, kWave), y1, __shfl(a.c[0], kWave - 1, kWave));
+    auto advance = [&](auto at) {   // y past one block, at(q): its map
+        if constexpr (K == 1) {
+            y1 = fma(at(0), y1, at(1));
+        } else {
+            const double n1 = fma(at(1), y2, fma(at(0), y1, at(4)));
+            const double n2 = fma(at(3), y2, fma(at(2), y1, at(5)));
+            y1 = n1;
+            y2 = n2;
+        }
+    };
+    double in1 = y1, in2 = y2;
+    if constexpr (!WIDE) {
+        advance([&](int q) {
+            return __shfl(q < K * K ? a.m[q < K * K ? q : 0] : a.c[q < K * K ? 0 : q - K * K], kWave - 1, kWave);
+        });
     } else {
-        my1 = fma(p.m[1], y2, fma(p.m[0], y1, p.c[0]));
-        my2 = fma(p.m[3], y2, fma(p.m[2], y1, p.c[1]));
-        const double t0 = __shfl(a.m[0], kWave - 1, kWave), t1 = __shfl(a.m[1], kWave - 1, kWave);
-        const double t2 = __shfl(a.m[2], kWave - 1, kWave), t3 = __shfl(a.m[3], kWave - 1, kWave);
-        const double c0 = __shfl(a.c[0], kWave - 1, kWave), c1 = __shfl(a.c[1], kWave - 1, kWave);
-        const double n1 = fma(t1, y2, fma(t0, y1, c0));
-        const double n2 = fma(t3, y2, fma(t2, y1, c1));
-        y1 = n1;
-        y2 = n2;
+        __syncthreads();   // the last call's maps have been read
+        if (lane == kWave - 1) {
+#pragma unroll
+            for (int q = 0; q < K * K; ++q) blk[wave][q] = a.m[q];
+#pragma unroll
+            for (int q = 0; q < K; ++q) blk[wave][K * K + q] = a.c[q];
+        }
+        __syncthreads();
+        for (int w = 0; w < waves; ++w) {
+            advance([&](int q) { return blk[w][q]; });
+            if (w + 1 == wave) {
+                in1 = y1;
+                in2 = y2;
+            }
+        }
+    }
+    if constexpr (K == 1) {
+        my1 = fma(p.m[0], in1, p.c[0]);
+        my2 = 0.0;
+    } else {
+        my1 = fma(p.m[1], in2, fma(p.m[0], in1, p.c[0]));
+        my2 = fma(p.m[3], in2, fma(p.m[2], in1, p.c[1]));
     }
 }
 
-// Grid: exactly m workgroups of one wave (system k = blockIdx.x).
-template <int K, int C, bool CYC, class Src>
-__global__ __launch_bounds__(64) void long_scan_spread(const double *__restrict__ table, CyclicQ cq,
+// Grid: exactly m workgroups (system k = blockIdx.x) of up to kSpreadWaves
+// waves; every wave runs the tail chunk, thread 0 stores it.  WIDE: more than
+// one wave (the VGPRs that these may take cost one-wave launches of many
+// systems their occupancy: penta n = 2000, m = 4095 80 us against 74).
+template <int K, int C, bool CYC, class Src, bool WIDE>
+__global__ __launch_bounds__(WIDE ? kSpreadWaves * kWave : kWave) void long_scan_spread(const double *__restrict__ table, CyclicQ cq,
                                                        LongGeom g, Src src, double *x)
 {
     using SP = FromScalar<double>;
     const int64_t k = blockIdx.x;
-    const int lane = threadIdx.x;
+    __shared__ double blk[kSpreadWaves][K * K + K];
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int waves = WIDE ? blockDim.x / kWave : 1;
+    const int row = waves * kWave;   // chunks per round of the workgroup
     const int64_t ld = g.ld;
     const int full = g.P - 1;
     const int na = num_arrays(K, CYC);
@@ -538,15 +581,15 @@ __global__ __launch_bounds__(64) void long_scan_spread(const double *__restrict_
     const double *Mb = Mf + (int64_t)g.P * K * K;
     const double *Gm = Mb + (int64_t)g.P * K * K;
 
-    // forward: H_j written over e_j; lane l of block j0 holds chunk j0 + l
+    // forward: H_j written over e_j; lane l of block jb holds chunk jb + l
     // (clamped to the last full chunk for the loads past it)
     double h1 = 0.0, h2 = 0.0;
     auto fwd_at = [&](int j) { return spread_fwd<K, C>(x, Mf, j < full ? j : full - 1, k, ld); };
-    SpreadFwd<K> cur = fwd_at(lane), nxt = fwd_at(kWave + lane);
-    for (int j0 = 0; j0 < full; j0 += kWave) {
-        const int cnt = full - j0 < kWave ? full - j0 : kWave;
-        // two blocks in flight ahead of the chain
-        const SpreadFwd<K> nn = fwd_at(j0 + 2 * kWave + lane);
+    SpreadFwd<K> cur = fwd_at(wave * kWave + lane), nxt = fwd_at(row + wave * kWave + lane);
+    for (int j0 = 0; j0 < full; j0 += row) {
+        const int jb = j0 + wave * kWave, cnt = full - jb;   // chunks from the wave's block on
+        // the next two rounds' blocks in flight during the chain
+        const SpreadFwd<K> nn = fwd_at(jb + 2 * row + lane);
         ChunkMap<K> a = identity_map<K>();
         if (lane < cnt) {
 #pragma unroll
@@ -555,19 +598,19 @@ __global__ __launch_bounds__(64) void long_scan_spread(const double *__restrict_
             if constexpr (K == 2) a.c[1] = cur.e2;
         }
         double my1, my2;
-        chain_block<K>(a, lane, h1, h2, my1, my2);
+        chain_blocks<K, WIDE>(a, blk, wave, waves, lane, h1, h2, my1, my2);
         if (lane < cnt) {
-            double *p = x + (int64_t)(j0 + lane) * C * ld + k;
+            double *p = x + (int64_t)(jb + lane) * C * ld + k;
             p[0] = my1;
             if constexpr (K == 2) p[ld] = my2;
         }
         cur = nxt;
         nxt = nn;
     }
-    // the H_j stored by one lane are read back by another below
-    __threadfence_block();
+    // the H_j stored by one wave are read back by another below
+    __syncthreads();
 
-    // the tail chunk (every lane the same; lane 0 stores it, uncorrected if
+    // the tail chunk (every lane the same; thread 0 stores it, uncorrected if
     // periodic)
     const int trow0 = full * C;
     const int nr = g.n - trow0;
@@ -598,16 +641,17 @@ __global__ __launch_bounds__(64) void long_scan_spread(const double *__restrict_
         });
         f1 = v[0];
         f2 = K == 2 ? v[1] : 0.0;
-        if (lane == 0) store_chunk<double, C, false>(v, x, trow0, k, ld, g.n);
+        if (threadIdx.x == 0) store_chunk<double, C, false>(v, x, trow0, k, ld, g.n);
     }
 
-    // backward: F_j written over o_j; lane l of block jt holds chunk jt - l
+    // backward: F_j written over o_j; lane l of block jb holds chunk jb - l
     // (clamped to chunk 0)
     auto bwd_at = [&](int j) { return spread_bwd<K, C>(x, Mb, Gm, j >= 0 ? j : 0, k, ld); };
-    SpreadBwd<K> bcur = bwd_at(full - 1 - lane), bnxt = bwd_at(full - 1 - kWave - lane);
-    for (int jt = full - 1; jt >= 0; jt -= kWave) {
-        const int cnt = jt + 1 < kWave ? jt + 1 : kWave;
-        const SpreadBwd<K> bnn = bwd_at(jt - 2 * kWave - lane);
+    SpreadBwd<K> bcur = bwd_at(full - 1 - wave * kWave - lane);
+    SpreadBwd<K> bnxt = bwd_at(full - 1 - row - wave * kWave - lane);
+    for (int jt = full - 1; jt >= 0; jt -= row) {
+        const int jb = jt - wave * kWave, cnt = jb + 1;
+        const SpreadBwd<K> bnn = bwd_at(jb - 2 * row - lane);
         ChunkMap<K> a = identity_map<K>();
         if (lane < cnt) {
 #pragma unroll
@@ -616,9 +660,9 @@ __global__ __launch_bounds__(64) void long_scan_spread(const double *__restrict_
             if constexpr (K == 2) a.c[1] = bcur.s2;
         }
         double my1, my2;
-        chain_block<K>(a, lane, f1, f2, my1, my2);
+        chain_blocks<K, WIDE>(a, blk, wave, waves, lane, f1, f2, my1, my2);
         if (lane < cnt) {
-            double *p = x + (int64_t)(jt - lane) * C * ld + k;
+            double *p = x + (int64_t)(jb - lane) * C * ld + k;
             p[(int64_t)K * ld] = my1;
             if constexpr (K == 2) p[(int64_t)(K + 1) * ld] = my2;
         }
@@ -631,12 +675,12 @@ __global__ __launch_bounds__(64) void long_scan_spread(const double *__restrict_
         const double rn2 = K == 2 ? fma(cq.u1_nm2, rn1, yn2) : 0.0;
         double c0 = 0.0, c1 = 0.0;
         correction_scalars<double, K>(cq, f1, f2, rn2, rn1, c0, c1);
-        for (int j = lane; j < full; j += kWave) {
+        for (int j = threadIdx.x; j < full; j += row) {
             double *p = x + ((int64_t)j * C + 2 * K) * ld + k;
             p[0] = c0;
             if constexpr (K == 2) p[ld] = c1;
         }
-        if (lane == 0) {
+        if (threadIdx.x == 0) {
             // the tail again, corrected (this lane stored it above)
             double v[C];
             load_chunk<double, C, false>(v, x, trow0, k, ld, g.n);
@@ -663,8 +707,12 @@ hipError_t launch_long_c(const double *table, const CyclicQ &q, const LongGeom &
                        table, g, src, x);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (g.spread)
-        hipLaunchKernelGGL((long_scan_spread<K, C, CYC, Src>), dim3((unsigned)g.m), dim3(kWave), 0,
+    const int wide = g.m <= kSpreadWide ? std::min((g.P - 2) / kWave + 1, kSpreadWaves) : 1;
+    if (g.spread && wide > 1)
+        hipLaunchKernelGGL((long_scan_spread<K, C, CYC, Src, true>), dim3((unsigned)g.m), dim3(wide * kWave), 0,
+                           s, table, q, g, src, x);
+    else if (g.spread)
+        hipLaunchKernelGGL((long_scan_spread<K, C, CYC, Src, false>), dim3((unsigned)g.m), dim3(kWave), 0,
                            s, table, q, g, src, x);
     else
         hipLaunchKernelGGL((long_scan<K, C, CYC, Src>), dim3((unsigned)sblocks), dim3(threads), 0,
