@@ -36,16 +36,16 @@ KERNEL_SOURCES = ("sweep_core.h", "sweep_kernel.h", "sweep.hip", "sweep_f32.hip"
                   "cn_stencil.h", "cn_tri.hip", "cn_penta.hip", "long_core.h", "long_sweep.hip",
                   "long_f32in.hip", "sweep_f32in.hip",
                   "adjoint_grad_kernel.h", "adjoint_grad_tri.hip", "adjoint_grad_penta.hip",
-                  "internal.h")
+                  "row_bcast.h", "strided_sum.h", "internal.h")
 # the device sources behind each kernel whose HBM traffic is recorded
 KERNEL_FAMILIES = {
-    "sweep": ("sweep_core.h", "sweep_kernel.h", "sweep.hip", "internal.h"),
-    "refine": ("sweep_core.h", "refine_kernel.h", "refine.hip", "internal.h"),
-    "stepper_cn": ("sweep_core.h", "stepper.h", "cn_stencil.h", "cn_tri.hip", "internal.h"),
-    "stepper_ch": ("sweep_core.h", "stepper.h", "ch.hip", "internal.h"),
-    "stepper_forced": ("sweep_core.h", "stepper.h", "ch_forced.hip", "internal.h"),
-    "long": ("sweep_core.h", "long_core.h", "long_sweep.hip", "internal.h"),
-    "adjoint_grad": ("sweep_core.h", "adjoint_grad_kernel.h", "adjoint_grad_tri.hip", "internal.h"),
+    "sweep": ("sweep_core.h", "row_bcast.h", "sweep_kernel.h", "sweep.hip", "internal.h"),
+    "refine": ("sweep_core.h", "row_bcast.h", "refine_kernel.h", "refine.hip", "internal.h"),
+    "stepper_cn": ("sweep_core.h", "row_bcast.h", "stepper.h", "cn_stencil.h", "cn_tri.hip", "internal.h"),
+    "stepper_ch": ("sweep_core.h", "row_bcast.h", "stepper.h", "ch.hip", "internal.h"),
+    "stepper_forced": ("sweep_core.h", "row_bcast.h", "stepper.h", "ch_forced.hip", "internal.h"),
+    "long": ("sweep_core.h", "row_bcast.h", "long_core.h", "long_sweep.hip", "internal.h"),
+    "adjoint_grad": ("sweep_core.h", "row_bcast.h", "adjoint_grad_kernel.h", "adjoint_grad_tri.hip", "internal.h"),
 }
 
 
