@@ -113,7 +113,8 @@ constexpr int grad_stage_len()
 
 // QL: log2 of the waves per system group; SL: log2 of the systems per group
 // (S = 64 Q / P); SCALAR: one chunk per wave with the coefficients through
-// the scalar cache (then P == Q and S = 64), else the table staged in LDS.
+// the scalar cache (then P == Q and S = 64), else by row broadcast from a table
+// staged in LDS.
 template <int K, int C, int QL, bool CYC, bool SCALAR, int SL>
 __global__ __launch_bounds__((kWave << QL) > kMaxBlockThreads ? (kWave << QL) : kMaxBlockThreads)
 void adjoint_grad_kernel(const double *__restrict__ table, int64_t table_elems, CyclicQ cq,

@@ -184,16 +184,16 @@ int split_log2(int log2P, int C, int n, bb::Op op, bool f32_in = false)
 // Decomposition of the fused steppers (Cahn-Hilliard, Crank-Nicolson).
 struct StepPlan {
     int C, P, log2P, log2Q;
-    bool scalar;   // one chunk per wave, coefficients through the scalar cache
+    bool scalar;   // one chunk per wave, coefficients through the scalar cache or by row broadcast
     int waves = 0; // > 0: that, on as many waves as n has chunks (P), any number up to 8
 };
 
 // Rows per lane: 64 (two waves per SIMD), or latency_chunk for small
-// batches, or 32 below two waves per SIMD where that keeps one chunk per wave.  Systems split over several waves when the chunks tile n: one
-// chunk per wave with scalar coefficients up to 8 chunks (also where they do
-// not tile n), else the LDS table
-// with 32 systems per group (4 waves at P = 8, 8 waves from P = 16; n = 1024,
-// m = 2^16: 0.063 vs 0.096 ms per tri step over one wave per group).
+// batches, or 32 below two waves per SIMD where that keeps one chunk per wave.
+// Systems split over several waves: one chunk per wave up to 8 chunks (also
+// where they do not tile n), else, when the chunks tile n, the LDS table with
+// 32 systems per group (4 waves at P = 8, 8 waves from P = 16; n = 1024,
+// m = 2^16: 34 against 96 us per tri step over one wave per group).
 // A tridiagonal group of 16 chunks that keeps its state on chip runs as 16
 // systems on 4 waves, three groups a CU (periodic n = 1024, m = 2^16, 50 steps:
 // 29 us a step against 34 with 32 systems on 8 waves, one group a CU, whose
@@ -842,9 +842,8 @@ bb_status ch_steps(bb_factor fh, const double *c_in, double *c_out, int64_t m, i
         g_last_error.clear();
         return BB_OK;
     }
-    // The fused steps are bound by arithmetic and coefficient reads, not HBM
-    // (64 rows per lane, two waves per SIMD: 0.39 vs 0.52 ms per step at
-    // n = 256, m = 2^20 against 128 rows per lane); see step_plan.
+    // The fused steps are bound by arithmetic and its latency, not HBM; see
+    // step_plan.
     StepPlan pl;
     bb::DeviceTable tab;
     bb::SweepGeom g;

@@ -28,8 +28,8 @@
 // Every wave of reduce and solve works on one chunk of 64 systems (one
 // 512-byte segment per row, or two 256-byte ones for large batches), so
 // every coefficient is the same for the whole wave: the table is read
-// through the scalar cache and may have any size.  HBM traffic: the right-hand side read twice and the solution
-// written once (24 B per row in double) plus 2K doubles per chunk of
+// through the scalar cache and may have any size.  HBM traffic: the
+// right-hand side read twice and the solution written once (24 B per row in double) plus 2K doubles per chunk of
 // scratch, against 16 B for the one-launch sweep.  x must not overlap the
 // right-hand side.
 #pragma once

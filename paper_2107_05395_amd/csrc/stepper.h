@@ -3,7 +3,7 @@
 // explicit stencil, possibly nonlinear) and solves the shared banded LHS,
 // `steps` times per launch, reading the batch once and writing it once.
 // The right-hand-side rule is a policy (Rhs); ch.hip (Cahn-Hilliard, Section
-// 5.1) and cn.hip (Crank-Nicolson diffusion and hyperdiffusion, Sections 3
+// 5.1) and cn_stencil.h (Crank-Nicolson diffusion and hyperdiffusion, Sections 3
 // and 4 benchmark problems) instantiate it.
 //
 // An Rhs policy provides
