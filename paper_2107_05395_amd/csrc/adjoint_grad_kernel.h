@@ -147,7 +147,7 @@ void adjoint_grad_kernel(const double *__restrict__ table, int64_t table_elems, 
     }
 
     LaneGeom lg = lane_geom(SCALAR ? QL : QL + 6 - SL, QL);
-    if constexpr (SCALAR) lg.j = lg.j0;
+    if constexpr (SL == 6) lg.j = lg.j0;   // one chunk per wave
     const int lane = threadIdx.x % kWave;
     const int n = g.n;
     const int row0 = lg.j * C;
@@ -260,8 +260,14 @@ void adjoint_grad_kernel(const double *__restrict__ table, int64_t table_elems, 
 }
 
 // The kernels this file builds: the LDS-table split kernel for 32- and 64-row
-// chunks in groups of 4 or 8 waves (S = 16 tri only, or 32), and the scalar
-// kernel for 32- and 64-row chunks (S = 64).
+// chunks in groups of 4 or 8 waves (S = 16 tri only, or 32), and kernels with
+// one chunk of 32 or 64 rows per wave (S = 64): coefficients by row broadcast
+// in groups of 8 waves, else through the scalar cache (us per call of 10 steps,
+// scalar vs broadcast: tri n = 512, m = 2^16 810 vs 683, penta 1044 vs 848;
+// penta n = 256, m = 20000 227 vs 203; not in 4 waves of 32 rows, tri n = 128,
+// m = 20000 69.9 vs 72.2).
+constexpr bool grad_by_rows(int log2Q) { return log2Q == 3; }
+
 template <int K>
 constexpr bool grad_lds_slots_ok(int SL)
 {
@@ -275,7 +281,7 @@ hipError_t adjoint_grad_go(const double *table, int64_t table_elems, const Cycli
                            size_t lds, hipStream_t s)
 {
     auto kern = adjoint_grad_kernel<K, C, QL, CYC, SCALAR, SL>;
-    if (SCALAR)
+    if (SL == 6)
         return launch_grid_mode(kern, lds, g.groups, 1 << QL, g.linear, s, table, table_elems, q, g,
                                 steps, lam_in, traj, traj_stride, lam_out, part);
     // one workgroup per group in launch order (no persistent loop): in a
@@ -305,7 +311,7 @@ hipError_t adjoint_grad_dispatch(const double *table, int64_t table_elems, const
             case 0: BB_AG(64, 0, true, 6);
             case 1: BB_AG(64, 1, true, 6);
             case 2: BB_AG(64, 2, true, 6);
-            case 3: BB_AG(64, 3, true, 6);
+            case 3: BB_AG(64, 3, false, 6);
             default: return hipErrorInvalidValue;
             }
         }
@@ -314,7 +320,7 @@ hipError_t adjoint_grad_dispatch(const double *table, int64_t table_elems, const
             case 0: BB_AG(32, 0, true, 6);
             case 1: BB_AG(32, 1, true, 6);
             case 2: BB_AG(32, 2, true, 6);
-            case 3: BB_AG(32, 3, true, 6);
+            case 3: BB_AG(32, 3, false, 6);
             default: return hipErrorInvalidValue;
             }
         }

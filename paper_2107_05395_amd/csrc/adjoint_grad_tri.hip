@@ -37,7 +37,7 @@ size_t adjoint_grad_lds(int K, const SweepGeom &g, bool scalar, int64_t table_el
         stage = sl == 4 ? grad_stage_len<1, 4>() : sl == 5 ? grad_stage_len<1, 5>() : grad_stage_len<1, 6>();
     else
         stage = sl == 5 ? grad_stage_len<2, 5>() : grad_stage_len<2, 6>();
-    const int64_t elems = (scalar ? 0 : table_elems) + split_exchange_len(K, g.log2Q) +
+    const int64_t elems = (scalar && !grad_by_rows(g.log2Q) ? 0 : table_elems) + split_exchange_len(K, g.log2Q) +
                           ((int64_t)stage << g.log2Q);
     return (size_t)elems * sizeof(double);
 }
