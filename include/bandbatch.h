@@ -127,9 +127,13 @@ int64_t bb_max_n(void);
  * lane (chunk), lanes per system (lanes, chunk * lanes >= n), waves per system
  * group (waves), and for the fused steppers whether every wave works on one
  * chunk (scalar; then lanes == waves, any number up to 8, otherwise lanes is a
- * power of two and waves 1, 2, 4 or 8).  what = 0: a solve or adjoint of precision p; what = 1:
- * the fused steppers (bb_ch_step, bb_ch_step_stats, bb_ch_forced_step,
- * bb_cn_step, bb_cn_trajectory; p is ignored).  Host only: no device is touched.  The tuning
+ * power of two and waves 1, 2, 4 or 8).  what = 0: a solve or adjoint of
+ * precision p; what = 1: the fused steppers where they keep their state on chip
+ * (bb_ch_step, bb_ch_step_stats, bb_ch_forced_step, bb_cn_step of more than one
+ * step; p is ignored); what = 3: the steppers that store every state
+ * (bb_cn_trajectory, bb_cn_step of one step, bb_adjoint_trajectory and the fused
+ * bb_adjoint_band_grad), whose groups of tridiagonal systems of 16 64-row chunks
+ * span 8 waves instead of 4.  Host only: no device is touched.  The tuning
  * variables of the library are honoured.  Any out pointer may be NULL.
  * Errors: BB_ERR_ARG (NULL factor, m < 1, what or p unknown). */
 bb_status bb_plan(bb_factor f, int64_t m, int32_t what, bb_precision p, int32_t *chunk,

@@ -637,7 +637,8 @@ bb_status bb_plan(bb_factor fh, int64_t m, int32_t what, bb_precision p, int32_t
 {
     if (!fh) return fail(BB_ERR_ARG, "factor is NULL");
     if (m < 1) return fail(BB_ERR_ARG, "m < 1");
-    if (what != 0 && what != 1) return fail(BB_ERR_ARG, "what must be 0 (solve) or 1 (fused steps)");
+    if (what != 0 && what != 1 && what != 3)
+        return fail(BB_ERR_ARG, "what must be 0 (solve), 1 (fused steps) or 3 (fused steps, states stored)");
     if (p != BB_F64 && p != BB_F32_REFINE && p != BB_F32 && p != BB_F32_RHS_REFINE &&
         p != BB_F32_RHS_F64)
         return fail(BB_ERR_ARG, "unknown precision");
@@ -659,7 +660,7 @@ bb_status bb_plan(bb_factor fh, int64_t m, int32_t what, bb_precision p, int32_t
                         : p == BB_F32_RHS_REFINE ? bb::Op::RefineF32Rhs : bb::Op::Solve;
         log2Q = split_log2(log2P, C, (int)f.n, op, p == BB_F32_RHS_F64);
     } else {
-        const StepPlan pl = step_plan(f.K, f.n, m);
+        const StepPlan pl = step_plan(f.K, f.n, m, what == 3);
         C = pl.C;
         P = pl.P;
         log2Q = pl.log2Q;

@@ -190,10 +190,14 @@ class Factor:
                 m, ld, _stream_ptr(rhs)))
         return out
 
-    def plan(self, m: int, stepper: bool = False, precision: str = "f64") -> dict:
-        """The decomposition a call with m systems takes (host only)."""
+    def plan(self, m: int, stepper: bool = False, precision: str = "f64",
+             states: bool = False) -> dict:
+        """The decomposition a call with m systems takes (host only): a solve,
+        with `stepper` the fused steps, with `states` too the steps that store
+        every state (trajectories, one step a call)."""
         out = [ctypes.c_int32() for _ in range(4)]
-        check(lib().bb_plan(self._handle, int(m), 1 if stepper else 0, _lib.PRECISION[precision],
+        what = (3 if states else 1) if stepper else 0
+        check(lib().bb_plan(self._handle, int(m), what, _lib.PRECISION[precision],
                             *(ctypes.byref(o) for o in out)))
         return dict(chunk=out[0].value, lanes=out[1].value, waves=out[2].value,
                     scalar=bool(out[3].value))
