@@ -108,9 +108,12 @@ bb_status bb_factor_destroy(bb_factor f);
  * device now, instead of on the first solve.  The copy is synchronous: the
  * tables are on the device when the call returns, and `stream` is not used
  * (kept so that the call can later be made asynchronous without an ABI
- * change).  A call whose decomposition differs (a small batch: fewer than
- * 2^16 lanes of 64-row chunks; the fused steppers) builds its own table on
- * first use.  That first call allocates device memory; make it before
+ * change).  The tables are those of solves and adjoints in FP64 and FP32 and
+ * of the fused steppers with 64-row chunks, and of ragged steppers (n that no
+ * power-of-two number of chunks tiles) with 32-row chunks as well.  A call whose
+ * decomposition differs (a small batch: fewer than 2^16 lanes of 64-row chunks;
+ * fused steps of fewer than 2^17 where 32-row chunks tile n) builds its own table
+ * on first use.  That first call allocates device memory; make it before
  * capturing the calls in a HIP graph. */
 bb_status bb_factor_upload(bb_factor f, void *stream);
 

@@ -400,18 +400,21 @@ bb_status stepper_too_long(const bb::Factor &f)
                                         std::to_string(bb::kMaxNPenta) + ")");
 }
 
+// The table of a stepper: that of a solve (or adjoint solve) with this chunk
+// size, or (key slot 4 = 3) of as many chunks as n has, not a power of two.
+bb_status stepper_table(bb::Factor &f, int dev, bool adjoint, const StepPlan &pl, bb::DeviceTable *tab)
+{
+    const bb::Direction &dir = adjoint ? f.adjoint : f.primal;
+    return device_table(f, f.dev, std::make_tuple(dev, (int)adjoint, 0, pl.C, pl.waves > 0 ? 3 : 0), false,
+                        [&] { return bb::build_sweep_table(dir, f.K, f.cyclic, f.n, pl.C, pl.P); }, tab);
+}
+
 bb_status stepper_setup(bb::Factor &f, int dev, int64_t m, int64_t ld, StepPlan *pl,
                         bb::DeviceTable *tab, bb::SweepGeom *g, bool adjoint, bool states)
 {
     if (is_long(f)) return stepper_too_long(f);
     *pl = step_plan(f.K, f.n, m, states);
-    const int C = pl->C, P = pl->P;
-    // the same table as a solve (or adjoint solve) with this chunk size
-    const bb::Direction &dir = adjoint ? f.adjoint : f.primal;
-    // (key slot 4 = 3: as many chunks as n has, not a power of two)
-    bb_status st = device_table(f, f.dev, std::make_tuple(dev, (int)adjoint, 0, C, pl->waves > 0 ? 3 : 0), false,
-                                [&] { return bb::build_sweep_table(dir, f.K, f.cyclic, f.n, C, P); },
-                                tab);
+    bb_status st = stepper_table(f, dev, adjoint, *pl, tab);
     if (st != BB_OK) return st;
     *g = step_geom(f.n, m, ld, *pl);
     return BB_OK;
@@ -627,6 +630,15 @@ bb_status bb_factor_upload(bb_factor fh, void *stream)
                               [&] { return bb::build_sweep_table(dir, f.K, f.cyclic, f.n, C, P); }, &t);
             if (st != BB_OK) return st;
         }
+    }
+    // ragged steppers of one chunk per wave have a table of their own, with
+    // 32- or 64-row chunks by the lanes in flight (step_plan: the line is 2^17)
+    const int64_t lanes = bb::lanes_for(f.n, 64);
+    for (int64_t in_flight : {int64_t(1) << 16, int64_t(1) << 17}) {
+        const StepPlan pl = step_plan(f.K, f.n, (in_flight + lanes - 1) / lanes);
+        bb::DeviceTable t;
+        for (int adj = 0; pl.waves > 0 && adj < 2; ++adj)
+            if ((st = stepper_table(f, dev, adj != 0, pl, &t)) != BB_OK) return st;
     }
     g_last_error.clear();
     return BB_OK;
