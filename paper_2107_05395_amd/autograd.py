@@ -49,10 +49,11 @@ def _side_stream(device, which: int) -> "torch.cuda.Stream":
 
 
 def _band_grads(gb, devices):
-    """The rows of gb on the bands' devices, one copy per device: a copy to the
-    host waits for the device each time."""
+    """The rows of gb on the bands' devices, one transfer per device (a copy to
+    the host waits for the device each time) and there a tensor per band, so
+    that resizing or saving one band's gradient leaves the others alone."""
     on = {d: gb.to(d) for d in set(devices)}
-    return [on[d][q] for q, d in enumerate(devices)]
+    return [gb[q] if d == gb.device else on[d][q].clone() for q, d in enumerate(devices)]
 
 
 def _kind(nb: int) -> str:
