@@ -33,8 +33,8 @@ __device__ __forceinline__ void stencil_rows8(double *c, double r, double &s, co
 {
     double sb, t1, t2, t3;
     asm(BB_W1_4("sa", "sb", "c0", "c1", "c2", "c3", "c4") BB_W1_4("sb", "sa", "c4", "c5", "c6", "c7", "r")
-        : [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3]), [c4] "+v"(c[4]),
-          [c5] "+v"(c[5]), [c6] "+v"(c[6]), [c7] "+v"(c[7]), [sa] "+v"(s), [sb] "=&v"(sb),
+        : [c0] "+&v"(c[0]), [c1] "+&v"(c[1]), [c2] "+&v"(c[2]), [c3] "+&v"(c[3]), [c4] "+&v"(c[4]),
+          [c5] "+&v"(c[5]), [c6] "+&v"(c[6]), [c7] "+&v"(c[7]), [sa] "+&v"(s), [sb] "=&v"(sb),
           [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3)
         : [r] "v"(r), [w0] "s"(w[0]), [w1] "s"(w[1]), [w2] "s"(w[2]));
 }
@@ -63,8 +63,8 @@ __device__ __forceinline__ void stencil_rows8(double *c, double r0, double r1, d
     double qa, qb, t2, t3;
     asm(BB_W2_4("u", "v", "qa", "qb", "c0", "c1", "c2", "c3", "c4", "c5")
         BB_W2_4("qa", "qb", "u", "v", "c4", "c5", "c6", "c7", "r0", "r1")
-        : [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3]), [c4] "+v"(c[4]),
-          [c5] "+v"(c[5]), [c6] "+v"(c[6]), [c7] "+v"(c[7]), [u] "+v"(u), [v] "+v"(v),
+        : [c0] "+&v"(c[0]), [c1] "+&v"(c[1]), [c2] "+&v"(c[2]), [c3] "+&v"(c[3]), [c4] "+&v"(c[4]),
+          [c5] "+&v"(c[5]), [c6] "+&v"(c[6]), [c7] "+&v"(c[7]), [u] "+&v"(u), [v] "+&v"(v),
           [qa] "=&v"(qa), [qb] "=&v"(qb), [t2] "=&v"(t2), [t3] "=&v"(t3)
         : [r0] "v"(r0), [r1] "v"(r1), [w0] "s"(w[0]), [w1] "s"(w[1]), [w2] "s"(w[2]), [w3] "s"(w[3]),
           [w4] "s"(w[4]));

@@ -11,8 +11,10 @@
 // not fold the broadcast into v_fmac_f64 (it emits v_mov_b64_dpp and the
 // product).  Each block opens with s_nop 1: a DPP operand may not be read
 // within two wait states of a VALU write, and the compiler, which does not
-// see into the block, may have moved a coefficient just before it.  Nothing
-// in a block is a memory access.  Operation order and rounding are those of
+// see into the block, may have moved a coefficient just before it.  Operands
+// written before the last one is read are early clobbers (+&v): without that an
+// input of the same value would share their registers.  Nothing in a block is a
+// memory access.  Operation order and rounding are those of
 // chunk_solve's plain passes.
 #pragma once
 
@@ -52,8 +54,8 @@ __device__ __forceinline__ RowCoef<C> row_coef(const double *base)
     [v0] "v"(v[t]), [v1] "v"(v[t + 1]), [v2] "v"(v[t + 2]), [v3] "v"(v[t + 3]), [v4] "v"(v[t + 4]), \
         [v5] "v"(v[t + 5]), [v6] "v"(v[t + 6]), [v7] "v"(v[t + 7])
 #define BB_V_IO(v, t)                                                                              \
-    [v0] "+v"(v[t]), [v1] "+v"(v[t + 1]), [v2] "+v"(v[t + 2]), [v3] "+v"(v[t + 3]),                \
-        [v4] "+v"(v[t + 4]), [v5] "+v"(v[t + 5]), [v6] "+v"(v[t + 6]), [v7] "+v"(v[t + 7])
+    [v0] "+&v"(v[t]), [v1] "+&v"(v[t + 1]), [v2] "+&v"(v[t + 2]), [v3] "+&v"(v[t + 3]),                \
+        [v4] "+&v"(v[t + 4]), [v5] "+&v"(v[t + 5]), [v6] "+&v"(v[t + 6]), [v7] "+&v"(v[t + 7])
 
 // pass 1, rows t .. t+7: e += wE v, o += wS v (K = 2: two of each)
 #define BB_P1K1(v, lane) BB_FMAC("e1", "we1", v, lane) BB_FMAC("o1", "ws1", v, lane)
@@ -66,11 +68,11 @@ __device__ __forceinline__ void rows8_ends(const double (&v)[C], double &e1, dou
 {
     if constexpr (T / 8 % 2 == 0)
         asm("s_nop 1\n\t" BB_ROWS_UP(BB_P1K1, 0, 1, 2, 3, 4, 5, 6, 7)
-            : [e1] "+v"(e1), [o1] "+v"(o1)
+            : [e1] "+&v"(e1), [o1] "+&v"(o1)
             : [we1] "v"(we1), [ws1] "v"(ws1), BB_V_IN(v, T));
     else
         asm("s_nop 1\n\t" BB_ROWS_UP(BB_P1K1, 8, 9, 10, 11, 12, 13, 14, 15)
-            : [e1] "+v"(e1), [o1] "+v"(o1)
+            : [e1] "+&v"(e1), [o1] "+&v"(o1)
             : [we1] "v"(we1), [ws1] "v"(ws1), BB_V_IN(v, T));
 }
 
@@ -80,11 +82,11 @@ __device__ __forceinline__ void rows8_ends(const double (&v)[C], double &e1, dou
 {
     if constexpr (T / 8 % 2 == 0)
         asm("s_nop 1\n\t" BB_ROWS_UP(BB_P1K2, 0, 1, 2, 3, 4, 5, 6, 7)
-            : [e1] "+v"(e1), [o1] "+v"(o1), [e2] "+v"(e2), [o2] "+v"(o2)
+            : [e1] "+&v"(e1), [o1] "+&v"(o1), [e2] "+&v"(e2), [o2] "+&v"(o2)
             : [we1] "v"(we1), [ws1] "v"(ws1), [we2] "v"(we2), [ws2] "v"(ws2), BB_V_IN(v, T));
     else
         asm("s_nop 1\n\t" BB_ROWS_UP(BB_P1K2, 8, 9, 10, 11, 12, 13, 14, 15)
-            : [e1] "+v"(e1), [o1] "+v"(o1), [e2] "+v"(e2), [o2] "+v"(o2)
+            : [e1] "+&v"(e1), [o1] "+&v"(o1), [e2] "+&v"(e2), [o2] "+&v"(o2)
             : [we1] "v"(we1), [ws1] "v"(ws1), [we2] "v"(we2), [ws2] "v"(ws2), BB_V_IN(v, T));
 }
 
@@ -223,12 +225,12 @@ __device__ __forceinline__ void rows8_correct(double (&v)[C], double c0, double 
 #define BB_DOWNK2(a, b, c, d)                                                                      \
     BB_AFF("e3", "g3", "h1", "h2", d) BB_AFF("e2", "g2", "e3", "g3", c)                            \
     BB_AFF("e1", "g1", "e2", "g2", b) BB_AFF("e0", "g0", "e1", "g1", a)
-#define BB_E_IO [e0] "+v"(e[0]), [e1] "+v"(e[1]), [e2] "+v"(e[2]), [e3] "+v"(e[3])
+#define BB_E_IO [e0] "+&v"(e[0]), [e1] "+&v"(e[1]), [e2] "+&v"(e[2]), [e3] "+&v"(e[3])
 #define BB_CHAIN1(SEQ)                                                                             \
     asm("s_nop 1\n\t" SEQ : BB_E_IO : [m0] "v"(m[0]), [h1] "v"(h1))
 #define BB_CHAIN2(SEQ)                                                                             \
     asm("s_nop 1\n\t" SEQ                                                                          \
-        : BB_E_IO, [g0] "+v"(g[0]), [g1] "+v"(g[1]), [g2] "+v"(g[2]), [g3] "+v"(g[3])              \
+        : BB_E_IO, [g0] "+&v"(g[0]), [g1] "+&v"(g[1]), [g2] "+&v"(g[2]), [g3] "+&v"(g[3])              \
         : [m0] "v"(m[0]), [m1] "v"(m[1]), [m2] "v"(m[2]), [m3] "v"(m[3]), [h1] "v"(h1), [h2] "v"(h2))
 
 template <int K, bool UP, int LANE0>
