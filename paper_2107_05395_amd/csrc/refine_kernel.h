@@ -20,15 +20,25 @@ constexpr int refine_waves(int K, int C, int QL, size_t rhs_bytes)
 // Steps of the group's scans per block: one for tridiagonal systems, whose
 // kernel has no registers to hold four at two waves per SIMD (n = 512,
 // m = 2^19, FP32 right-hand sides: 873 us with four, 781 with one); four for
-// pentadiagonal ones (n = 1024, m = 2^17: 690 us, 704 with one).
+// pentadiagonal ones (n = 1024, m = 2^17: 690 us, 704 with one).  The
+// step-by-step scans stop at the lane's own chunk and pass the periodic end
+// states round: every wave walking all chunks, which needs no third phase,
+// took (us, double and FP32 right-hand sides) periodic n = 1024, m = 300 23.6
+// and 18.4 against 17.3 and 14.4, n = 2048, m = 50001 830 and 729 against 731
+// and 628; at 8 chunks the barrier costs about that much (periodic n = 512,
+// m = 2^18 583 and 387 against 567 and 401).
 template <int K>
 constexpr int kRefineSteps = K == 1 ? 1 : 4;
+
+// arrays of P*S values in chunk_solve's exchange area (split_exchange_len, and
+// the end states of the step-by-step scans)
+constexpr int refine_phases(int K, bool cyclic) { return 2 * K + (K == 1 && cyclic ? 2 : 0); }
 
 // ---------------------------------------------------------------- refine
 // x0 = solve_f32(b); r = b - A x0 in double with the original bands;
 // x = x0 + solve_f32(r), stored as double.
-// QL > 0: split groups as in sweep_kernel; the exchange area holds the two
-// phases of chunk_solve followed by rows 0, 1, C-2, C-1 of every chunk.
+// QL > 0: split groups as in sweep_kernel; the exchange area holds the phases
+// of chunk_solve followed by rows 0, 1, C-2, C-1 of every chunk.
 // TB: type of the right-hand sides in memory -- double, or float when the
 // right-hand sides are FP32 data (promoted exactly for the residual).
 template <int K, int C, bool CYC, bool FULL, int QL, typename TB>
@@ -76,7 +86,7 @@ void refine_kernel(
         float xl1, xl2, xr1, xr2, r0 = 0.f, r1 = 0.f, rn2 = 0.f, rn1 = 0.f;
         if constexpr (QL > 0) {
             const int PS = lg.P * lg.S;
-            float *xd = xch + 2 * K * PS;   // [4][P*S]: rows 0, 1, C-2, C-1 of (chunk, slot)
+            float *xd = xch + refine_phases(K, CYC) * PS;   // [4][P*S]: rows 0, 1, C-2, C-1 of (chunk, slot)
             const int me = lg.j * lg.S + lg.sl;
             xd[me] = x0[0];
             xd[PS + me] = x0[1];
@@ -170,7 +180,7 @@ hipError_t refine_c(const void *table, int64_t table_elems, const double *band,
         if constexpr (C >= 32) {
             if (!is_full(g) || g.log2Q > max_log2q(C, true) || g.log2Q > g.log2P)
                 return hipErrorInvalidValue;
-            const size_t xl = (size_t)(split_exchange_len(K, g.log2Q) + (4LL * kWave << g.log2Q)) * sizeof(float);
+            const size_t xl = (size_t)((refine_phases(K, CYC) + 4LL) * kWave << g.log2Q) * sizeof(float);
             if (g.log2Q == 1)
                 return launch_grid_split(refine_kernel<K, C, CYC, true, 1, TB>, lds + xl, g.groups, 2,
                                          stream, (const float *)table, table_elems, band,
