@@ -34,8 +34,14 @@ void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, 
     const LaneGeom lg = lane_geom(g.log2P, QL);
     const int row0 = lg.j * C;
     // ragged: only the waves that hold the last real chunk or padding take the
-    // loads and stores with a predicate and a pointer select per row
-    const bool all_real = FULL || (QL > 0 && (lg.j0 + lg.W) * C <= g.n);
+    // loads and stores with a predicate and a pointer select per row.  FP32
+    // sweeps take them in every wave: a second path of loads costs the
+    // tridiagonal kernel its fourth wave per SIMD (us: tri n = 600, m = 50001 53
+    // with one path, 72 with two; n = 1025, m = 2^14 38 and 47; periodic n = 600,
+    // m = 50001 53 and 78; penta n = 600, m = 2^18 388 and 427; the other way at
+    // tri n = 2000, m = 2^16: 441 and 387)
+    constexpr bool F64 = std::is_same<T, double>::value;
+    const bool all_real = FULL || (F64 && QL > 0 && (lg.j0 + lg.W) * C <= g.n);
     const GroupRange gr = group_range(g.groups, QL, g.linear);
     for (int64_t b = gr.first; b < gr.end; b += gr.stride) {
         const int64_t grp = begin_block(gr, b, g.lockstep);
@@ -62,7 +68,7 @@ void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, 
         // is pending in the compiler's books when the loop comes round; it
         // would hold the next group's loads until this group's stores are done
         // (tri n = 1000, m = 2^16: 234 against 390 us)
-        if constexpr (!FULL) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+        if constexpr (!FULL && F64) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
         chunk_solve<T, K, C, CYC, FULL, (QL > 0), FromLds<T>, ROWS>(v, lds, lg, g.n, cq, xch);
         if (kval) {
             if (all_real)
