@@ -17,10 +17,10 @@ constexpr int refine_waves(int K, int C, int QL, size_t rhs_bytes)
     return (K == 1 && C == 64 && QL == 2 && rhs_bytes == 4) || QL == 3 ? 2 : 1;
 }
 
-// Steps of the group's scans per block: one for tridiagonal systems, whose
-// kernel has no registers to hold four at two waves per SIMD (n = 512,
-// m = 2^19, FP32 right-hand sides: 873 us with four, 781 with one); four for
-// pentadiagonal ones (n = 1024, m = 2^17: 690 us, 704 with one).  The
+// Steps of the group's scans per block: none (step by step) for tridiagonal
+// systems, whose kernel has no registers to hold four at two waves per SIMD
+// (n = 512, m = 2^19, FP32 right-hand sides: 873 us with four, 781 with one);
+// four for pentadiagonal ones (n = 1024, m = 2^17: 690 us, 704 with one).  The
 // step-by-step scans stop at the lane's own chunk and pass the periodic end
 // states round: every wave walking all chunks, which needs no third phase,
 // took (us, double and FP32 right-hand sides) periodic n = 1024, m = 300 23.6
@@ -28,7 +28,7 @@ constexpr int refine_waves(int K, int C, int QL, size_t rhs_bytes)
 // and 628; at 8 chunks the barrier costs about that much (periodic n = 512,
 // m = 2^18 583 and 387 against 567 and 401).
 template <int K>
-constexpr int kRefineSteps = K == 1 ? 1 : 4;
+constexpr int kRefineSteps = K == 1 ? 0 : 4;
 
 // arrays of P*S values in chunk_solve's exchange area (split_exchange_len, and
 // the end states of the step-by-step scans)

@@ -401,10 +401,10 @@ __device__ __forceinline__ void rows_correct(double (&v)[C], const double *tab, 
 // ROWS: the passes take their coefficients by row broadcast (row_bcast.h):
 // double, table in LDS, S a multiple of 16 so that a 16-lane row works on one
 // chunk.
-// BL: steps per block of the group's scans; 1 (K = 1, FULL) walks no further
-// than the lane's own chunk, one load and step at a time, and passes the
-// periodic end states round in a third phase of the exchange area, of 2 P S
-// elements more: for kernels without the registers of a block's loads.
+// BL: steps per block of the group's scans; 0 (K = 1, FULL): no blocks, each
+// lane walks to its own chunk, one load and step at a time, and the periodic end
+// states go round in a third phase of the exchange area, of 2 P S elements more
+// (for kernels without the registers of a block's loads).
 template <typename T, int K, int C, bool CYC, bool FULL, bool SPLIT = false,
           typename Src = FromLds<T>, bool ROWS = false, int BL = 4>
 __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, const LaneGeom &lg,
@@ -413,7 +413,7 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
     static_assert(!ROWS || (std::is_same<T, double>::value && std::is_same<Src, FromLds<T>>::value &&
                             C % kRowLanes == 0),
                   "row-broadcast coefficients: double, LDS table, 16-row blocks");
-    static_assert(!SPLIT || BL > 1 || (K == 1 && FULL && !ROWS), "step-by-step scans");
+    static_assert(!SPLIT || BL > 0 || (K == 1 && FULL && !ROWS), "step-by-step scans");
     // array indices of the table (internal.h)
     constexpr int qE = 0, qW = K, qs = 2 * K, ql = 2 * K + 1, qu = 3 * K + 1;
     constexpr bool ZROWS = CYC && !FULL;   // the table has z arrays
@@ -465,7 +465,7 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
         xa[me] = e1;
         if constexpr (K == 2) xa[PS + me] = e2;
         __syncthreads();
-        if constexpr (BL == 1) {
+        if constexpr (BL == 0) {
             for (int i = 0; i < lg.j; ++i) h1 = fma(tb.Mf[i], h1, xa[i * lg.S + lg.sl]);
         } else {
             group_scan<T, K, ROWS, true, CYC, BL>(xa, mats, lg, real, h1, h2, y1e, y2e);
@@ -496,7 +496,7 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
         xb[me] = s1;
         if constexpr (K == 2) xb[PS + me] = s2;
         __syncthreads();
-        if constexpr (BL == 1) {
+        if constexpr (BL == 0) {
             for (int i = lg.P - 1; i > lg.j; --i) f1 = fma(tb.Mb[i], f1, xb[i * lg.S + lg.sl]);
         } else {
             group_scan<T, K, ROWS, false, CYC, BL>(xb, mats + lg.P * K * K, lg, lg.P, f1, f2, x0e, x1e);
@@ -514,7 +514,7 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
     // y_{n-1} and x_{n-2} = y_{n-2} - u1 y_{n-1})
     T c0 = T(0), c1 = T(0);
     if constexpr (CYC) {
-        if constexpr (SPLIT && BL == 1) {
+        if constexpr (SPLIT && BL == 0) {
             T *xc = xch + 2 * PS;   // [2][P*S]: every chunk's start and forward end state
             xc[me] = fma(tb.Mb[lg.j], f1, s1);
             xc[PS + me] = fma(tb.Mf[lg.j], h1, e1);
