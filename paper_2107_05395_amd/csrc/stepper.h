@@ -97,7 +97,12 @@ __global__ __launch_bounds__(kMaxBlockThreads) void step_kernel(const double *__
         const int64_t k = grp * lg.S + lg.sl;
         const bool kval = k < g.m;
         double c[C];
-        load_chunk<double, C, FULL>(c, in, row0, kval ? k : g.m - 1, g.ld, g.n);
+        // rows selected as they come: waiting for all of them first costs a
+        // launch of few steps up to a tenth (trajectory of 4 states, tri n = 777,
+        // m = 8192: 117 against 105 us, n = 1000, m = 8192 186 and 169; one step,
+        // penta n = 777, m = 2^16 424 and 409).  The other way round for periodic
+        // pentadiagonal systems (n = 600, m = 2^16 400 and 411 us a step)
+        load_chunk<double, C, FULL, K == 2 && CYC>(c, in, row0, kval ? k : g.m - 1, g.ld, g.n);
         const typename Rhs::State ls = rhs.lane_state(kval ? k : g.m - 1, row0);
 
         for (int64_t step = 0; step < steps; ++step) {

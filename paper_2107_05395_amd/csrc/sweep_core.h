@@ -682,7 +682,9 @@ __device__ __forceinline__ void stage_table(T *lds, const T *__restrict__ table,
 // Ragged: the row pointer stops at row n-1 (in bounds) and rows past n read 0.
 // The stride is laundered once per call so the C row offsets are recomputed
 // here rather than hoisted out of the persistent loop and kept live.
-template <typename T, int C, bool FULL>
+// ALL (ragged): every load in flight before the first is looked at; otherwise
+// each row is selected as it comes.
+template <typename T, int C, bool FULL, bool ALL = true>
 __device__ __forceinline__ void load_chunk(T (&v)[C], const T *base, int row0, int64_t k,
                                            int64_t ld, int n)
 {
@@ -696,14 +698,16 @@ __device__ __forceinline__ void load_chunk(T (&v)[C], const T *base, int row0, i
         const T *p = base + (int64_t)(row0 < n ? row0 : n - 1) * ld + k;
 #pragma unroll
         for (int t = 0; t < C; ++t) {
-            v[t] = *p;
+            const T x = *p;
+            v[t] = ALL || t < nv ? x : T(0);
             p += (t + 1 < nv) ? ld : 0;
         }
-        // all loads in flight before the first is looked at: left to itself the
-        // compiler may wait for each in turn
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (ALL) {
+            // left to itself the compiler may wait for each in turn
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int t = 0; t < C; ++t) v[t] = t < nv ? v[t] : T(0);
+            for (int t = 0; t < C; ++t) v[t] = t < nv ? v[t] : T(0);
+        }
     }
 }
 
