@@ -35,7 +35,7 @@ void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, 
     const int row0 = lg.j * C;
     // ragged: only the waves that hold the last real chunk or padding take the
     // loads and stores with a predicate and a pointer select per row.  FP32
-    // sweeps take them in every wave: a second path of loads costs the
+    // sweeps take them in every wave, row by row: a second path of loads costs the
     // tridiagonal kernel its fourth wave per SIMD (us: tri n = 600, m = 50001 53
     // with one path, 72 with two; n = 1025, m = 2^14 38 and 47; periodic n = 600,
     // m = 50001 53 and 78; penta n = 600, m = 2^18 388 and 427; the other way at
@@ -54,7 +54,7 @@ void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, 
             if (all_real)
                 load_chunk<T, C, true>(v, in, row0, kk, g.ld, g.n);
             else
-                load_chunk<T, C, false>(v, in, row0, kk, g.ld, g.n);
+                load_chunk<T, C, false, F64>(v, in, row0, kk, g.ld, g.n);
         } else {
             TI w[C];
             if (all_real)
