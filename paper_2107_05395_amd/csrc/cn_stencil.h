@@ -208,6 +208,13 @@ struct StencilLongSrc {
     }
 };
 
+// Three waves, as the other sources' kernels have: in 162 VGPRs without spills;
+// left alone the compiler takes 184 and two (periodic n = 2049, m = 5000, one
+// step: 91 us at two, 83 at three; n = 1500, m = 6000 86 and 80; the other way at
+// n = 4000, m = 50001, 1197 and 1226).
+template <>
+constexpr int kSolveWaves<StencilLongSrc<2, true>> = 3;
+
 template <int K>
 hipError_t launch_cn_long_k(bool cyclic, const double *table, const CyclicQ &q, const LongGeom &g,
                             const double *w, const double *in, double *out, hipStream_t s)

@@ -324,8 +324,13 @@ __global__ __launch_bounds__(256) void long_scan(const double *__restrict__ tabl
     }
 }
 
+// Waves per SIMD long_solve is held to, by its source (1: as many as its
+// registers leave).
+template <class Src>
+constexpr int kSolveWaves = 1;
+
 template <int K, int C, bool CYC, class Src>
-__global__ __launch_bounds__(256) void long_solve(const double *__restrict__ table, LongGeom g,
+__global__ __launch_bounds__(256, kSolveWaves<Src>) void long_solve(const double *__restrict__ table, LongGeom g,
                                                   Src src, double *x)
 {
     const LongWave lw = long_wave(g);
