@@ -42,7 +42,7 @@ KERNEL_FAMILIES = {
     "sweep": ("sweep_core.h", "row_bcast.h", "sweep_kernel.h", "sweep.hip", "internal.h"),
     "refine": ("sweep_core.h", "row_bcast.h", "refine_kernel.h", "refine.hip", "internal.h"),
     "stepper_cn": ("sweep_core.h", "row_bcast.h", "stepper.h", "cn_stencil.h", "cn_tri.hip", "internal.h"),
-    "stepper_ch": ("sweep_core.h", "row_bcast.h", "stepper.h", "ch.hip", "internal.h"),
+    "stepper_ch": ("sweep_core.h", "row_bcast.h", "stepper.h", "ch.hip", "strided_sum.h", "internal.h"),
     "stepper_forced": ("sweep_core.h", "row_bcast.h", "stepper.h", "ch_forced.hip", "internal.h"),
     "long": ("sweep_core.h", "row_bcast.h", "long_core.h", "long_sweep.hip", "internal.h"),
     "adjoint_grad": ("sweep_core.h", "row_bcast.h", "adjoint_grad_kernel.h", "adjoint_grad_tri.hip", "internal.h"),

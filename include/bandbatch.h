@@ -416,11 +416,12 @@ bb_status bb_mse_loss_grad(const double *u, const double *target, double *grad, 
  *   "waves_per_system"  waves per split system group: 1, 2, 4 or 8 where valid
  *   "waves_per_block"   waves per workgroup of unsplit sweeps: 1, 2 or 4
  *   "lockstep"          0 / 1: a workgroup barrier at every persistent iteration
- *   "ch_uniform"        0: the fused steppers never read coefficients through
- *                       the scalar cache
- *   "grid_linear"       0 / 1: persistent grids / one workgroup per group
+ *   "ch_uniform"        0: no fused stepper with one chunk per wave
+ *   "grid_linear"       0 / 1: persistent grids / one workgroup per group (ragged
+ *                       steppers of one chunk per wave: always the latter)
  *   "long_spread"       0 / 1: the scan of long systems with one lane per system
- *                       / one wave per system (automatic: a wave for m < 4096)
+ *                       / one workgroup per system (automatic: the latter for
+ *                       m < 4096)
  * The settings are read when a call enqueues its launches; change them only
  * between calls.  Errors: BB_ERR_ARG (unknown name, invalid value). */
 bb_status bb_set_tuning(const char *name, int64_t value);

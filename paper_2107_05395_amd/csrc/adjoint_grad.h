@@ -8,9 +8,9 @@
 namespace bb {
 
 // Whether the fused kernel runs the stepper decomposition g (split groups or
-// one chunk per wave with scalar coefficients; full decomposition), and its
-// LDS bytes.  table_elems: elements of the LDS-staged table (ignored when
-// scalar).
+// one chunk per wave; full decomposition), and its LDS bytes.  table_elems:
+// elements of the coefficient table, which every group stages in LDS but those of
+// one chunk per wave on fewer than 8 waves (scalar cache).
 bool adjoint_grad_supported(int K, const SweepGeom &g, bool scalar);
 size_t adjoint_grad_lds(int K, const SweepGeom &g, bool scalar, int64_t table_elems);
 

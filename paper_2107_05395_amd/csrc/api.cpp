@@ -124,13 +124,15 @@ int solve_chunk(int64_t n, int64_t m, bb_precision p)
 // Tuning lockstep = 0/1 overrides.
 // Grid shape.  Persistent grids (at most one wave of resident workgroups,
 // each walking its XCD's share of the groups) serve the kernels that stage
-// a coefficient table in LDS, once per workgroup.  The scalar-coefficient
-// stepper stages nothing and runs one workgroup per group in launch order
-// (measured, CH n = 256, m = 2^20, one step per launch: 0.855 vs 0.953 ms;
-// the LDS kernels lose: tri FP32+refine n = 512, m = 2^20 2.64 vs 2.04 ms,
-// penta n = 1024 FP64 1.04 vs 0.99 ms).  Tuning grid_linear = 0/1 forces
-// persistent / one-per-group grids everywhere (tuning; the launcher reads the
-// same setting for the LDS kernels).  Returns -1 when unset.
+// a coefficient table in LDS, once per workgroup.  The steppers with one chunk
+// per wave run one workgroup per group in launch order: those that read the
+// scalar cache stage nothing (measured, CH n = 256, m = 2^20, one step per
+// launch: 0.855 vs 0.953 ms), those by row broadcast read their table from L2 and
+// still gain (launch_stepper); the other LDS kernels lose (tri FP32+refine
+// n = 512, m = 2^20 2.64 vs 2.04 ms, penta n = 1024 FP64 1.04 vs 0.99 ms).
+// Tuning grid_linear = 0/1 forces persistent / one-per-group grids (tuning; the
+// launcher reads the same setting for the LDS kernels) but for ragged steppers of
+// one chunk per wave, whose kernel has the one grid.  Returns -1 when unset.
 int grid_linear() { return (int)bb::tuning(bb::kTuneGridLinear); }
 
 int lockstep_for(bool split)
@@ -199,8 +201,8 @@ struct StepPlan {
 // 29 us a step against 34 with 32 systems on 8 waves, one group a CU, whose
 // waves all wait at its barriers together); with every state stored (states)
 // the rows' 256-byte segments of 32 systems matter more.
-// Tuning max_chunk, ch_uniform = 0 (no scalar kernel) and waves_per_system =
-// 1/2/4/8 override (tuning, testing).
+// Tuning max_chunk, ch_uniform = 0 (no kernel with one chunk per wave) and
+// waves_per_system = 1/2/4/8 override (tuning, testing).
 StepPlan step_plan(int K, int64_t n, int64_t m, bool states = false)
 {
     int C = bb::choose_chunk(n, std::min(max_chunk(BB_F64), bb::kChunkMaxCH));
@@ -208,7 +210,7 @@ StepPlan step_plan(int K, int64_t n, int64_t m, bool states = false)
         const int64_t lanes64 = m * bb::lanes_for(n, C);
         C = latency_chunk(n, m, C);
         // Fewer than two waves per SIMD at 64 rows: 32-row chunks (still one
-        // per wave, scalar coefficients) double the waves.  Measured, ms per
+        // per wave) double the waves.  Measured, ms per
         // 200 fused steps, 64 vs 32 rows: penta n = 64, m = 2^16 0.84 vs
         // 0.71; n = 128, m = 2^15 1.18 vs 0.80; n = 256, m = 2^14 1.22 vs
         // 0.98; CH n = 64, m = 2^16 0.87 vs 0.67; equal or worse from 2^17

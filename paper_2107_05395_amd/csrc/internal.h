@@ -33,8 +33,9 @@
 // through a small LDS exchange area (barriers instead of shuffles).  The
 // solve kernel splits any decomposition with C >= 64, the refinement kernel
 // only full ones (P*C == n); the fused steppers (stepper.h) split full 32- and
-// 64-row decompositions, into one chunk per wave with the coefficients in
-// scalar registers up to P = 8, else with the table in LDS.
+// 64-row decompositions, and ragged ones into one chunk per wave up to P = 8.
+// With one chunk per wave their coefficients come through the scalar cache or by
+// row broadcast from LDS (chunk_by_rows), else from the table in LDS.
 //
 // Coefficient table (one per direction, precision and chunk size)
 // ----------------------------------------------------------------
@@ -145,7 +146,7 @@ enum TuneKey : int {
     kTuneWavesPerSystem,     // split-group width 1, 2, 4 or 8 where valid
     kTuneWavesPerBlock,      // waves per workgroup of unsplit sweeps: 1, 2 or 4
     kTuneLockstep,           // 0 / 1: workgroup barrier per persistent iteration
-    kTuneChUniform,          // 0: no scalar-coefficient stepper kernel
+    kTuneChUniform,          // 0: no stepper kernel with one chunk per wave
     kTuneGridLinear,         // 0 / 1: persistent or one-workgroup-per-group grids
     kTuneLongSpread,         // 0 / 1: long-system scan with one lane or one workgroup per system
     kTuneCount
@@ -194,9 +195,11 @@ hipError_t launch_refine_f32rhs(int K, bool cyclic, const void *table, int64_t t
                                 void *out, hipStream_t stream);
 
 // Cahn-Hilliard steps with the state resident on chip (cyclic penta, double).
-// scalar: one 64-row chunk per wave with scalar coefficients (log2Q ==
-// log2P <= 3); else log2Q > 0 splits a full decomposition (C = 32, 64) over
-// 2^log2Q waves with the table in LDS, and log2Q == 0 keeps one wave per group.
+// scalar: one chunk per wave, coefficients through the scalar cache or by row
+// broadcast from LDS (16, 32 or 64 rows, log2Q == log2P <= 3; or on g.waves waves,
+// 32 or 64 rows, the last chunk with padding); else log2Q > 0 splits a full
+// decomposition (C = 32, 64) over 2^log2Q waves with the table in LDS, and
+// log2Q == 0 keeps one wave per group.
 // With partial != nullptr and samples >= 1, also the typical domain size:
 // lbar[s] = mean over the m runs of 1 / (1 - <c^2>) after (s + 1) * every
 // steps; partial is a workspace of g.groups * samples doubles.

@@ -398,7 +398,9 @@ __global__ __launch_bounds__(256, kSolveWaves<Src>) void long_solve(const double
 // of cross-lane moves, about 1 us): periodic penta
 // n = 16384, m = 8 24.4 us a solve against 32.6 with one wave per system, tri
 // n = 262144, m = 8 92 against 181.
-constexpr int kSpreadWaves = 8;   // a tail chunk of 64 rows needs their 256 VGPRs
+// (A tail chunk of 64 rows, which only tuning max_chunk gives a batch this small,
+// takes their 256 VGPRs; periodic, it spills 19 to 25, the forced step's 103.)
+constexpr int kSpreadWaves = 8;
 // One wave per system from here on: the waves of other systems fill the SIMDs
 // (penta n = 16384, m = 64 39.7 us with one wave, 31.3 with eight; m = 512
 // 96.2 and 99.7).

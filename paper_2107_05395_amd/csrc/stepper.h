@@ -179,11 +179,17 @@ __device__ __forceinline__ void row_at(double (&v)[C], int t, double &x)
 }
 
 // Waves per SIMD a split kernel is held to.  Three, with 64-row chunks in 168
-// VGPRs, where the compiler gets there without spills (a workgroup of four
-// waves or fewer, at most two halo rows): a step waits at its barriers and
-// for its recurrences, and the other workgroups of the CU fill in.  The
-// Cahn-Hilliard kernel with the statistic, 2 VGPRs over: 2746 us at two
-// (n = 256, m = 2^18, 50 steps).
+// VGPRs, in workgroups of four waves or fewer with at most two halo rows: a step
+// waits at its barriers and for its recurrences, and the other workgroups of the
+// CU fill in.  Most get there with a few VGPRs spilled (4-wave Cahn-Hilliard 4,
+// with the statistic 2, periodic penta 6, tri of 16 chunks 10; three full chunks,
+// periodic penta 22, penta 4, Cahn-Hilliard 16) and are faster all the same (us
+// for 20 steps, two waves and three; n = 256, m = 2^18: Cahn-Hilliard 958 and 822,
+// with the statistic 1149 and 967, periodic penta 961 and 769, penta, no spills,
+// 793 and 803; n = 192, m = 2^18: periodic penta 950 and 800, penta 883 and 655,
+// Cahn-Hilliard 949 and 772; tri n = 1024, m = 2^16: 606 and 600, periodic 605
+// and 569).  The spills cost launches that store every state: periodic penta
+// n = 192 one step 171 and 199 us, 4 states at m = 2^17 217 and 252.
 constexpr int step_waves(int K, int C, int QL, bool scalar, int rows, int R, int rag)
 {
     const bool three = C == 64 && QL <= 2 && R <= 2 && rag != kRagTail &&
@@ -400,7 +406,10 @@ constexpr size_t split_step_lds(int K, int QL, int R, bool stats, bool rag = fal
 // Launch `steps` fused steps.  `scalar` selects the kernels with one chunk
 // per wave (on g.waves waves, or on 2^log2Q == 2^log2P), otherwise
 // g.log2Q > 0 the split kernel (full decomposition, log2Q <= 3) with the table
-// in LDS, else the LDS kernel with one wave per group.  The grid of the
+// in LDS, else the LDS kernel with one wave per group.  The split kernel takes
+// its coefficients by row broadcast in groups of 16 64-row chunks and of 32
+// chunks, by plain LDS reads in the others: 16 32-row chunks (n = 512 in small
+// batches) fit the broadcast too, which has not been measured there.  The grid of the
 // kernels with one chunk per wave follows g.linear (one that stages a table
 // reads it from L2 and still gains: penta n = 512, m = 2^17, two steps per
 // launch 171 vs 149 us a step); the other LDS kernels stage the table once per
