@@ -52,8 +52,8 @@ def _band_grads(gb, devices):
     """The rows of gb on the bands' devices, one transfer per device (a copy to
     the host waits for the device each time) and there a tensor per band, so
     that resizing or saving one band's gradient leaves the others alone."""
-    on = {d: gb.to(d) for d in set(devices)}
-    return [gb[q] if d == gb.device else on[d][q].clone() for q, d in enumerate(devices)]
+    on = {d: torch.unbind_copy(gb.to(d)) for d in set(devices) if d != gb.device}
+    return [on[d][q] if d in on else gb[q] for q, d in enumerate(devices)]
 
 
 def _kind(nb: int) -> str:
