@@ -195,12 +195,12 @@ struct StepPlan {
 // Systems split over several waves: one chunk per wave up to 8 chunks (also
 // where they do not tile n), else, when the chunks tile n, the LDS table with
 // 32 systems per group (4 waves at P = 8, 8 waves from P = 16; n = 1024,
-// m = 2^16: 34 against 96 us per tri step over one wave per group).
+// m = 2^16: 30 against 96 us per tri step over one wave per group).
 // A tridiagonal group of 16 chunks that keeps its state on chip runs as 16
-// systems on 4 waves, three groups a CU (periodic n = 1024, m = 2^16, 50 steps:
-// 29 us a step against 34 with 32 systems on 8 waves, one group a CU, whose
-// waves all wait at its barriers together); with every state stored (states)
-// the rows' 256-byte segments of 32 systems matter more.
+// systems on 4 waves, three groups a CU (n = 1024, m = 2^16, 50 steps: 25.2 us a
+// step against 30.1 periodic, 28.6 not, with 32 systems on 8 waves, one group a
+// CU, whose waves all wait at its barriers together); with every state stored
+// (states) the rows' 256-byte segments of 32 systems matter more.
 // Tuning max_chunk, ch_uniform = 0 (no kernel with one chunk per wave) and
 // waves_per_system = 1/2/4/8 override (tuning, testing).
 StepPlan step_plan(int K, int64_t n, int64_t m, bool states = false)
