@@ -67,11 +67,24 @@ __device__ __forceinline__ double block_sum(double v, int S)
     return v;
 }
 
+// Whether a ragged group of one wave has all of a chunk's rows in flight before
+// it selects the first, rather than selecting each as it comes.  With 64-row
+// chunks the latter: launches of few steps start sooner (trajectory of 4 states,
+// tri n = 777, m = 8192: 117 against 102 us, n = 1000, m = 8192 191 and 175; one
+// step, penta n = 777, m = 2^16 424 and 409; 10 steps, periodic tri n = 1025,
+// m = 8192 888 and 848).  The former for pentadiagonal systems that are periodic
+// (n = 600, m = 2^16, states stored 400 against 411 us a step) or in shorter
+// chunks (n = 600, m = 1000, 10 steps 96 and 102), and for trajectories of periodic
+// tridiagonal systems of more than 16 chunks (4 states, n = 1025, m = 8192 447 and
+// 470; n = 1000, of 16, 207 and 185).
+constexpr bool step_rows_first(int K, bool cyclic, int C) { return K == 2 && (cyclic || C < 64); }
+
 // One lane per chunk; the lanes of a system sit in one wave (shuffles) and
 // the coefficient table is staged in LDS.
 // TRAJ: the state after every step s (0-based) is stored at
 // out + s * st.traj_stride instead of only the last one at out.
-template <class Rhs, int K, bool CYC, int C, bool FULL, bool STATS, bool TRAJ>
+template <class Rhs, int K, bool CYC, int C, bool FULL, bool STATS, bool TRAJ,
+          bool ALL = step_rows_first(K, CYC, C)>
 __global__ __launch_bounds__(kMaxBlockThreads) void step_kernel(const double *__restrict__ table,
                                                              int64_t table_elems, CyclicQ cq,
                                                              SweepGeom g, Rhs rhs, int64_t steps,
@@ -97,12 +110,7 @@ __global__ __launch_bounds__(kMaxBlockThreads) void step_kernel(const double *__
         const int64_t k = grp * lg.S + lg.sl;
         const bool kval = k < g.m;
         double c[C];
-        // rows selected as they come: waiting for all of them first costs a
-        // launch of few steps up to a tenth (trajectory of 4 states, tri n = 777,
-        // m = 8192: 117 against 105 us, n = 1000, m = 8192 186 and 169; one step,
-        // penta n = 777, m = 2^16 424 and 409).  The other way round for periodic
-        // pentadiagonal systems (n = 600, m = 2^16 400 and 411 us a step)
-        load_chunk<double, C, FULL, K == 2 && CYC>(c, in, row0, kval ? k : g.m - 1, g.ld, g.n);
+        load_chunk<double, C, FULL, ALL>(c, in, row0, kval ? k : g.m - 1, g.ld, g.n);
         const typename Rhs::State ls = rhs.lane_state(kval ? k : g.m - 1, row0);
 
         for (int64_t step = 0; step < steps; ++step) {
@@ -503,6 +511,10 @@ hipError_t launch_stepper(const double *table, int64_t table_elems, const Cyclic
 #undef BB_SPLIT
     }
     const size_t lds = (size_t)table_elems * sizeof(double);
+    if constexpr (K == 1 && CYC && TRAJ)
+        if (g.C == 64 && g.log2P >= 5 && !is_full(g))   // step_rows_first
+            return launch_grid(step_kernel<Rhs, K, CYC, 64, false, STATS, TRAJ, true>, lds, g.groups, s,
+                               table, table_elems, q, g, rhs, steps, st, in, out);
 #define BB_STEP(CC)                                                                            \
     case CC:                                                                                   \
         return is_full(g) ? launch_grid(step_kernel<Rhs, K, CYC, CC, true, STATS, TRAJ>, lds, g.groups, s,   \
