@@ -401,8 +401,8 @@ __device__ __forceinline__ void rows_correct(double (&v)[C], const double *tab, 
 // ROWS: the passes take their coefficients by row broadcast (row_bcast.h):
 // double, table in LDS, S a multiple of 16 so that a 16-lane row works on one
 // chunk.
-// BL: steps per block of the group's scans; 0 (K = 1, FULL): no blocks, each
-// lane walks to its own chunk, one load and step at a time, and the periodic end
+// BL: steps per block of the group's scans; 0 (K = 1, full or not periodic): no
+// blocks, each lane walks to its own chunk, one load and step at a time, and the periodic end
 // states go round in a third phase of the exchange area, of 2 P S elements more
 // (for kernels without the registers of a block's loads).
 template <typename T, int K, int C, bool CYC, bool FULL, bool SPLIT = false,
@@ -413,7 +413,7 @@ __device__ __forceinline__ void chunk_solve(T (&v)[C], typename Src::ptr tab, co
     static_assert(!ROWS || (std::is_same<T, double>::value && std::is_same<Src, FromLds<T>>::value &&
                             C % kRowLanes == 0),
                   "row-broadcast coefficients: double, LDS table, 16-row blocks");
-    static_assert(!SPLIT || BL > 0 || (K == 1 && FULL && !ROWS), "step-by-step scans");
+    static_assert(!SPLIT || BL > 0 || (K == 1 && (FULL || !CYC) && !ROWS), "step-by-step scans");
     // array indices of the table (internal.h)
     constexpr int qE = 0, qW = K, qs = 2 * K, ql = 2 * K + 1, qu = 3 * K + 1;
     constexpr bool ZROWS = CYC && !FULL;   // the table has z arrays

@@ -35,11 +35,13 @@ void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, 
     const int row0 = lg.j * C;
     // ragged: only the waves that hold the last real chunk or padding take the
     // loads and stores with a predicate and a pointer select per row.  FP32
-    // sweeps take them in every wave, row by row: a second path of loads costs the
-    // tridiagonal kernel its fourth wave per SIMD (us: tri n = 600, m = 50001 53
-    // with one path, 72 with two; n = 1025, m = 2^14 38 and 47; periodic n = 600,
-    // m = 50001 53 and 78; penta n = 600, m = 2^18 388 and 427; the other way at
-    // tri n = 2000, m = 2^16: 441 and 387)
+    // sweeps take them in every wave: a second path of loads costs the
+    // tridiagonal kernel its fourth wave per SIMD (us, one path and two: tri
+    // n = 600, m = 50001 52 and 72; n = 1025, m = 2^14 37 and 47; periodic n = 600,
+    // m = 50001 53 and 78; penta n = 600, m = 2^18 389 and 427; the other way at
+    // tri n = 2000, m = 2^16: 427 and 382).  Tridiagonal ones select each row as it
+    // comes (2 %), pentadiagonal ones all after the last load (n = 1000, m = 2^18
+    // 569 and 590, n = 600 389 and 380).
     constexpr bool F64 = std::is_same<T, double>::value;
     const bool all_real = FULL || (F64 && QL > 0 && (lg.j0 + lg.W) * C <= g.n);
     const GroupRange gr = group_range(g.groups, QL, g.linear);
@@ -54,7 +56,7 @@ void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, 
             if (all_real)
                 load_chunk<T, C, true>(v, in, row0, kk, g.ld, g.n);
             else
-                load_chunk<T, C, false, F64>(v, in, row0, kk, g.ld, g.n);
+                load_chunk<T, C, false, F64 || K == 2>(v, in, row0, kk, g.ld, g.n);
         } else {
             TI w[C];
             if (all_real)
@@ -69,7 +71,11 @@ void sweep_kernel(const T *__restrict__ table, int64_t table_elems, CyclicQ cq, 
         // would hold the next group's loads until this group's stores are done
         // (tri n = 1000, m = 2^16: 234 against 390 us)
         if constexpr (!FULL && F64) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
-        chunk_solve<T, K, C, CYC, FULL, (QL > 0), FromLds<T>, ROWS>(v, lds, lg, g.n, cq, xch);
+        // scans of the FP32 tridiagonal kernel of ragged systems step by step: in
+        // blocks, the padding chunks' steps cost small batches (n = 1025, m = 1000
+        // 12.4 us, 11.9 without)
+        constexpr int BL = !F64 && K == 1 && !CYC && !FULL ? 0 : 4;
+        chunk_solve<T, K, C, CYC, FULL, (QL > 0), FromLds<T>, ROWS, BL>(v, lds, lg, g.n, cq, xch);
         if (kval) {
             if (all_real)
                 store_chunk<T, C, true>(v, out, row0, k, g.ld, g.n);
